@@ -1012,9 +1012,16 @@ __global__ __launch_bounds__(kThreads, 2) void attn_units_kernel(DevPool P, Attn
 }
 
 // Log-sum-exp merge of a row's partials.  One wave per (list position,
-// query head): lane k < nk reads partial k's (max, sum), the wave reduces the
-// maximum and the weighted sum, then every lane accumulates its two d values
-// over the partials with the weights broadcast from their lanes.
+// query head): lane k < nk reads partial k's (max, sum) and the wave reduces
+// the maximum and the weighted sum, while the partials themselves are already
+// on their way: half-wave h reads partials 2 j + h whole (16 bytes a lane),
+// kMergeDepth of them per half requested before the first is used, the loads
+// past nk clamped to the last partial and left out of the sums.  Each half
+// adds its partials in order; the two halves' sums are added last.  Bound by
+// latency at small populations (a row's partials are 2-10 KB) and by HBM at
+// large ones (0.1 GB at 512 traces).
+constexpr int kMergeDepth = 8;
+
 __global__ __launch_bounds__(256) void merge_kernel(DevPool P, AttnLaunch A) {
   if (blockIdx.x == 0 && threadIdx.x < 8) A.queues[threadIdx.x] = 0;  // for the next attention launch
   if (A.len_bias && A.advance) {  // the step's token is in: advance the lengths (and GenLen, Alg. 1)
@@ -1025,14 +1032,22 @@ __global__ __launch_bounds__(256) void merge_kernel(DevPool P, AttnLaunch A) {
       P.gen[t] += 1;
     }
   }
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int row = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (row >= A.n * P.Hq) return;
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, half = lane >> 5;
   const int pos = row / P.Hq;
-  const int nk = A.nk[pos];  // <= kmax <= 64
+  const int nk = A.nk[pos];  // 1 <= nk <= kmax <= 64
   const float2* ml = A.part_ml + (size_t)row * A.kmax;
-  const float* pa = A.part_acc + (size_t)row * A.kmax * kHeadDim;
+  const float* pa = A.part_acc + (size_t)row * A.kmax * kHeadDim + 4 * (lane & 31);
   const float2 mine = lane < nk ? ml[lane] : float2{-INFINITY, 0.f};
+  f32x4 a[kMergeDepth];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int j = 0; j < kMergeDepth; ++j)
+      a[j] = __builtin_nontemporal_load(
+          reinterpret_cast<const f32x4*>(pa + (size_t)min(k0 + 2 * j + half, nk - 1) * kHeadDim));
+  };
+  load(0);
   float M = mine.x;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
@@ -1040,36 +1055,25 @@ __global__ __launch_bounds__(256) void merge_kernel(DevPool P, AttnLaunch A) {
   float L = w * mine.y;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) L += __shfl_xor(L, off);
-  // Partials are read once: eight loads in flight, streaming; added in
-  // partial order.
-  float o0 = 0.f, o1 = 0.f;
-  int k = 0;
-  for (; k + 8 <= nk; k += 8) {
-    f32x2 a[8];
+  f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int k0 = 0; k0 < nk; k0 += 2 * kMergeDepth) {
+    if (k0) load(k0);
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      a[j] = __builtin_nontemporal_load(reinterpret_cast<const f32x2*>(pa + (size_t)(k + j) * kHeadDim + 2 * lane));
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float wk = __shfl(w, k + j);
-      o0 += wk * a[j].x;
-      o1 += wk * a[j].y;
+    for (int j = 0; j < kMergeDepth; ++j) {
+      const int k = k0 + 2 * j + half;  // <= 63
+      const float wk = __shfl(w, k);
+      if (k < nk) o += wk * a[j];
     }
   }
-  for (; k < nk; ++k) {
-    const f32x2 a = __builtin_nontemporal_load(reinterpret_cast<const f32x2*>(pa + (size_t)k * kHeadDim + 2 * lane));
-    const float wk = __shfl(w, k);
-    o0 += wk * a.x;
-    o1 += wk * a.y;
-  }
   const float inv = 1.f / L;
-  o0 *= inv;
-  o1 *= inv;
-  if (A.out_f32) {
-    reinterpret_cast<float2*>(A.out)[(size_t)row * (kHeadDim / 2) + lane] = float2{o0, o1};
-  } else {
-    reinterpret_cast<uint32_t*>(A.out)[(size_t)row * (kHeadDim / 2) + lane] = pack_bf16x2(o0, o1);
-  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = (o[e] + __shfl_xor(o[e], 32)) * inv;
+  if (half) return;
+  const size_t at = (size_t)row * (kHeadDim / 4) + lane;
+  if (A.out_f32)
+    reinterpret_cast<f32x4*>(A.out)[at] = o;
+  else
+    reinterpret_cast<uint2*>(A.out)[at] = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
 }
 
 }  // namespace

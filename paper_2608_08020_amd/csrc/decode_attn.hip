@@ -241,33 +241,57 @@ __device__ inline void pv_mfma(const bf16x8 (&vf)[8], const bf16x8& ph, const bf
   }
 }
 
+// One unit, in scalar registers (one 64-byte scalar load; `u` is uniform over
+// the wave and the plan is not written while a launch reads it).
+typedef int32_t i32x16 __attribute__((ext_vector_type(16)));
+#define GAMBIT_CONST __attribute__((address_space(4)))
+__device__ inline AttnUnit load_unit(const AttnUnit* u) {
+  return __builtin_bit_cast(AttnUnit, *reinterpret_cast<const GAMBIT_CONST i32x16*>(reinterpret_cast<uintptr_t>(u)));
+}
+
+// Query row (list position x Hq + query head) of the lane's row of the row
+// block starting at row0, -1 past the unit's R rows.  The first four
+// members' positions are in the unit; a group of four heads or more has at
+// most four members in a row block, read with scalar loads (kMemberPad keeps
+// them in bounds); smaller groups read their member per lane.
+__device__ inline int query_row(const AttnLaunch& A, const AttnUnit& U, int Hq, int row0, int R, int lr) {
+  const int r = row0 + lr, gs = A.gshift;
+  int pos;
+  if (gs >= 2 && row0 < R) {
+    const int m0 = row0 >> gs, k = lr >> gs;
+    int p0 = U.pos[0], p1 = U.pos[1], p2 = U.pos[2], p3 = U.pos[3];
+    if (m0) {
+      const GAMBIT_CONST int32_t* m =
+          reinterpret_cast<const GAMBIT_CONST int32_t*>(reinterpret_cast<uintptr_t>(A.members + U.mem_off + m0));
+      p0 = m[0], p1 = m[1], p2 = m[2], p3 = m[3];
+    }
+    pos = k == 0 ? p0 : (k == 1 ? p1 : (k == 2 ? p2 : p3));
+  } else {
+    pos = r < R ? A.members[U.mem_off + (r >> gs)] : 0;
+    asm volatile("" : "+v"(pos));  // waited for here, not where the two ways meet
+  }
+  const int h = (U.kvh << gs) + (r & ((1 << gs) - 1));
+  return r < R ? pos * Hq + h : -1;
+}
+
 // Partials: lane (q, lr) holds O[row lr][16 r + 4 q + e] in acc[r][e].
-__device__ inline void write_partial(const DevPool& P, const AttnLaunch& A, const AttnUnit& U, int row0, int R,
-                                     int q, int lr, const RowState& st) {
+__device__ inline void write_partial(const AttnLaunch& A, const AttnUnit& U, int qrow, int q, const RowState& st) {
   const float l = wave_sum_over_groups(st.l);
-  const int r = row0 + lr;
-  if (r >= R) return;
-  const int g = P.g;
-  const int pos = A.members[U.mem_off + r / g];
-  const int h = U.kvh * g + r % g;
-  const size_t idx = ((size_t)pos * P.Hq + h) * A.kmax + U.kidx;
+  if (qrow < 0) return;
+  const size_t idx = (size_t)qrow * A.kmax + U.kidx;
   f32x4* dst = reinterpret_cast<f32x4*>(A.part_acc + idx * kHeadDim + 4 * q);
 #pragma unroll
   for (int k = 0; k < 8; ++k) __builtin_nontemporal_store(st.acc[k], dst + 4 * k);  // read once, by the merge
   if (q == 0) A.part_ml[idx] = float2{st.m, l};
 }
 
-// Q^T operand of the row block starting at row0: lane (q, lr) holds row
-// row0 + lr in the given d layout (zeros past the unit's rows).
-__device__ inline void load_q(const DevPool& P, const AttnLaunch& A, const AttnUnit& U, int row0, int R, bool fp8_direct,
-                              int q, int lr, bf16x8 (&qf)[4]) {
-  const int r = row0 + lr;
-  if (r < R) {
-    const int pos = A.members[U.mem_off + r / P.g];
-    const int h = U.kvh * P.g + r % P.g;
-    const uint16_t* qrow = A.q + ((size_t)pos * P.Hq + h) * kHeadDim;
+// Q^T operand of a row block: lane (q, lr) holds its row in the given d
+// layout (zeros past the unit's rows).
+__device__ inline void load_q(const AttnLaunch& A, int qrow, bool fp8_direct, int q, bf16x8 (&qf)[4]) {
+  if (qrow >= 0) {
+    const uint16_t* src = A.q + (size_t)qrow * kHeadDim;
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) qf[kb] = *reinterpret_cast<const bf16x8*>(qrow + q_offset(fp8_direct, kb, q));
+    for (int kb = 0; kb < 4; ++kb) qf[kb] = *reinterpret_cast<const bf16x8*>(src + q_offset(fp8_direct, kb, q));
   } else {
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) qf[kb] = bf16x8{};
@@ -276,10 +300,12 @@ __device__ inline void load_q(const DevPool& P, const AttnLaunch& A, const AttnU
 
 // The unit's block ids (and fp8 scales) 64 at a time, one per lane, read
 // back with readlane.  Window w + 1 is fetched when the tiles enter window
-// w, so a tile never waits on a table load.  Entries outside the pool are
-// never dereferenced: they become block 0 and the device error word records
-// them (bf16 checks the id when a tile takes it; fp8 when the window is
-// fetched, before its scales are read).
+// w, so a tile never waits on a table load; the first two tiles take their
+// ids from the unit itself (first_tile), so their loads do not wait for the
+// table either, and the first window's fp8 scales are asked for after those
+// loads.  Entries outside the pool are never dereferenced: they become block
+// 0 and the device error word records them (bf16 checks the id when a tile
+// takes it; fp8 when the window's scales are fetched).
 template <bool FP8>
 struct BlockIds {
   const DevPool& P;
@@ -290,41 +316,59 @@ struct BlockIds {
   int cur_id, nxt_id;
   float cur_ks, cur_vs, nxt_ks, nxt_vs;
 
-  __device__ BlockIds(const DevPool& P_, const int32_t* brow_, int nblk_, int lane_, int fresh_j_ = -1,
-                      int fresh_id_ = 0, float fresh_scale_ = 1.f)
-      : P(P_), brow(brow_), nblk(nblk_), lane(lane_), win(0), fresh_j(fresh_j_), fresh_id(fresh_id_),
-        fresh_scale(fresh_scale_) {
-    fetch(0, cur_id, cur_ks, cur_vs);
-    fetch(1, nxt_id, nxt_ks, nxt_vs);
+  __device__ BlockIds(const DevPool& P_, const int32_t* brow_, int nblk_, int lane_)
+      : P(P_), brow(brow_), nblk(nblk_), lane(lane_), win(0), fresh_j(-1), fresh_id(0), fresh_scale(1.f) {
+    cur_ks = cur_vs = nxt_ks = nxt_vs = 1.f;
+    nxt_id = 0;
+    cur_id = ids(0);
+    if (nblk > 64) nxt_id = ids(1);
   }
-  // Lanes past the unit's last block re-read its last entry (never used);
-  // the unconditional load lets the id land in place without a copy.
-  __device__ void fetch(int w, int& id, float& ks, float& vs) {
-    const int j = min(64 * w + lane, nblk - 1);
-    id = brow[j];
-    ks = vs = 1.f;
-    if (j == fresh_j) {
-      id = fresh_id;
+  // Lanes past the unit's last block re-read its last entry (never used).
+  __device__ int slot(int w) const { return min(64 * w + lane, nblk - 1); }
+  __device__ int ids(int w) const { return brow[slot(w)]; }
+  // The launch opened the unit's last block.
+  __device__ void opened(int id, float scale) {
+    fresh_j = nblk - 1;
+    fresh_id = id;
+    fresh_scale = scale;
+    if (slot(0) == fresh_j) cur_id = id;
+    if (nblk > 64 && slot(1) == fresh_j) nxt_id = id;
+  }
+  __device__ void scales(int w, int& id, float& ks, float& vs) const {
+    if (slot(w) == fresh_j) {
       ks = vs = fresh_scale;
       return;
     }
-    if constexpr (FP8) {
-      if ((unsigned)id >= (unsigned)P.num_blocks) {
-        atomicOr(P.err, kErrBadBlock);
-        id = 0;
-      }
-      ks = P.kv_scale[2 * id];
-      vs = P.kv_scale[2 * id + 1];
+    if ((unsigned)id >= (unsigned)P.num_blocks) {
+      atomicOr(P.err, kErrBadBlock);
+      id = 0;
     }
+    ks = P.kv_scale[2 * id];
+    vs = P.kv_scale[2 * id + 1];
   }
-  __device__ int checked(int b) {
-    if constexpr (!FP8) {
-      if ((unsigned)b >= (unsigned)P.num_blocks) {
-        if (lane == 0) atomicOr(P.err, kErrBadBlock);
-        b = 0;
-      }
+  __device__ void first_scales() {
+    scales(0, cur_id, cur_ks, cur_vs);
+    if (nblk > 64) scales(1, nxt_id, nxt_ks, nxt_vs);
+  }
+  __device__ int in_pool(int b) const {
+    if ((unsigned)b >= (unsigned)P.num_blocks) {
+      if (lane == 0) atomicOr(P.err, kErrBadBlock);
+      b = 0;
     }
     return b;
+  }
+  __device__ int checked(int b) const { return FP8 ? b : in_pool(b); }
+  // Blocks of tile i < 2: from the unit, or from the table for a block that
+  // was not there when the plan was made.
+  __device__ void first_tile(const AttnUnit& U, int i, int& b0, int& b1) const {
+    const int j0 = 2 * i, j1 = 2 * i + 1 < nblk ? 2 * i + 1 : 2 * i;
+    b0 = i ? U.first[2] : U.first[0];
+    b1 = j1 == j0 ? b0 : (i ? U.first[3] : U.first[1]);
+    if (b0 < 0 || b1 < 0) {
+      asm volatile("");  // a branch: the wait for the table stays out of the common path
+      b0 = in_pool(__builtin_amdgcn_readlane(cur_id, j0));
+      b1 = in_pool(__builtin_amdgcn_readlane(cur_id, j1));
+    }
   }
   // ids and scales of tile i (logical blocks 2 i and 2 i + 1, both in one
   // window; a missing second block aliases the first, its tokens are
@@ -336,7 +380,11 @@ struct BlockIds {
       cur_ks = nxt_ks;
       cur_vs = nxt_vs;
       ++win;
-      fetch(win + 1, nxt_id, nxt_ks, nxt_vs);
+      if (64 * (win + 1) < nblk) {
+        nxt_id = ids(win + 1);
+        if (slot(win + 1) == fresh_j) nxt_id = fresh_id;
+        if constexpr (FP8) scales(win + 1, nxt_id, nxt_ks, nxt_vs);
+      }
     }
     b0 = checked(__builtin_amdgcn_readlane(cur_id, j0 & 63));
     b1 = checked(__builtin_amdgcn_readlane(cur_id, j1 & 63));
@@ -521,26 +569,25 @@ __device__ inline uint32_t e4m3fn_code(float y) {
   return sign | c;
 }
 
-__device__ inline int fresh_block(const AttnLaunch& A, int pos) {
-  int lo = 0, hi = A.n_new;  // new_pos is ascending
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (A.new_pos[mid] < pos)
-      lo = mid + 1;
-    else
-      hi = mid;
+// The block that list position pos opens in this step (-1: not listed); the
+// wave compares 64 entries at a time.
+__device__ inline int fresh_block(const AttnLaunch& A, int pos, int lane) {
+  for (int k = 0; k < A.n_new; k += 64) {
+    const int i = k + lane;
+    const uint64_t hit = __builtin_amdgcn_ballot_w64(i < A.n_new && A.new_pos[i] == pos);
+    if (hit) return A.new_blk[k + __builtin_ctzll(hit)];
   }
-  return lo < A.n_new && A.new_pos[lo] == pos ? A.new_blk[lo] : -1;
+  return -1;
 }
 
 template <bool FP8>
 __device__ inline int append_token(const DevPool& P, const AttnLaunch& A, const AttnUnit& U, int lane, int len) {
   constexpr int es = FP8 ? 1 : 2;
   const int tpos = len - 1;
-  const int pos = A.members[U.mem_off];
+  const int pos = U.pos[0];
   int b, fresh = -1;
   if (A.len_bias && (tpos & 15) == 0) {
-    b = fresh = fresh_block(A, pos);
+    b = fresh = fresh_block(A, pos, lane);
     if ((unsigned)b < (unsigned)P.num_blocks && U.kvh == 0 && lane == 0) {
       if (A.claim) {
         P.table[(size_t)U.owner * P.max_blocks + (tpos >> 4)] = b;
@@ -605,30 +652,65 @@ __device__ inline int append_token(const DevPool& P, const AttnLaunch& A, const 
 template <bool FP8, int RB>
 __device__ void narrow_unit(const DevPool& P, const AttnLaunch& A, const AttnUnit& U, int lane, uint8_t* qlds) {
   const int32_t* brow = P.table + (size_t)U.owner * P.max_blocks + U.jb0;
-  const int len = U.nblk >= 0 ? 0 : P.seq_len[U.owner] + A.len_bias;
-  const int ntok = U.nblk >= 0 ? U.nblk * kBlock : len - U.jb0 * kBlock;
+  const bool open = U.nblk < 0;  // the run ends where its trace does, the new token included
+  const int len = open ? U.pos[1] + A.delta : 0;
+  const int ntok = open ? len - U.jb0 * kBlock : U.nblk * kBlock;
   if (ntok <= 0) return;
-  const int fresh = U.nblk < 0 ? append_token<FP8>(P, A, U, lane, len) : -1;
-  const int R = U.mem_cnt * P.g;  // <= 16 RB
+  const int R = U.mem_cnt << A.gshift;  // <= 16 RB
   const LaneGeom g = lane_geom(lane);
   const int nblk = (ntok + kBlock - 1) / kBlock;
   const int ntile = (ntok + 31) / 32;
-  BlockIds<FP8> ids(P, brow, nblk, lane, fresh >= 0 ? nblk - 1 : -1, fresh, A.new_scale);
+  // Everything the first tiles need is asked for at once: the queries, the
+  // table, the new token, then two tiles of K and V (their block ids are in
+  // the unit).  A launch of a few tiles per wave is a chain of such round
+  // trips (~1 us each under load): 64 traces 41.7 us, six layers of 45
+  // traces 31 us a launch when each of them waited for the one before.
+  BlockIds<FP8> ids(P, brow, nblk, lane);
+  int qrow[RB];
+  bf16x8 qf[RB][4];
+#pragma unroll
+  for (int r = 0; r < RB; ++r) {
+    qrow[r] = query_row(A, U, P.Hq, 16 * r, R, g.lr);
+    load_q(A, qrow[r], FP8, g.q, qf[r]);
+  }
+  if (open) {
+    const int fresh = append_token<FP8>(P, A, U, lane, len);
+    if (fresh >= 0) ids.opened(fresh, A.new_scale);
+    if (ntile <= 2) __builtin_amdgcn_s_waitcnt(0);  // the appended token is in the cache
+  }
+  const float sl = A.scale_log2;
+
+  auto fetch_k = [&](const TileMeta& m, Tile<FP8>& t) {
+    load_k<FP8>(P.k_cache + head_off<FP8>(m.b0, P.Hkv, U.kvh), P.k_cache + head_off<FP8>(m.b1, P.Hkv, U.kvh), g,
+                lane, t);
+  };
+  auto fetch_v = [&](const TileMeta& m, Tile<FP8>& t) {
+    load_v<FP8>(P.v_cache + head_off<FP8>(m.b0, P.Hkv, U.kvh), P.v_cache + head_off<FP8>(m.b1, P.Hkv, U.kvh), g, t);
+  };
+  auto meta = [&](int i, TileMeta& m) { ids.tile(i, m.b0, m.b1, m.ks0, m.ks1, m.vs0, m.vs1); };
+  Tile<FP8> ta, tb;
+  TileMeta ma{0, 0, 1.f, 1.f, 1.f, 1.f}, mb = ma, na{}, nb{};  // current and next (tile + 2) of buffers A and B
+  ids.first_tile(U, 0, ma.b0, ma.b1);
+  fetch_k(ma, ta);
+  fetch_v(ma, ta);
+  if (ntile > 1) {
+    ids.first_tile(U, 1, mb.b0, mb.b1);
+    fetch_k(mb, tb);
+    fetch_v(mb, tb);
+  }
+  RowState st[RB];
+#pragma unroll
+  for (int r = 0; r < RB; ++r) row_init(st[r]);
   // One row block keeps its Q operands in registers; two keep them in this
   // wave's LDS region (a narrow workgroup uses no other LDS) and read them
   // back for every tile, which leaves the registers to the two running
   // states and the tiles in flight.
-  bf16x8 qf[1][4];
-  RowState st[RB];
+  if constexpr (RB > 1) {
 #pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    load_q(P, A, U, 16 * r, R, FP8, g.q, g.lr, qf[0]);
-    if constexpr (RB > 1) {
+    for (int r = 0; r < RB; ++r)
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb)
-        *reinterpret_cast<bf16x8*>(qlds + (4 * r + kb) * 1024 + lane * 16) = qf[0][kb];
-    }
-    row_init(st[r]);
+        *reinterpret_cast<bf16x8*>(qlds + (4 * r + kb) * 1024 + lane * 16) = qf[r][kb];
   }
   auto scores = [&](const Tile<FP8>& t, f32x4 (&s0)[RB], f32x4 (&s1)[RB]) {
     if constexpr (RB == 1) {
@@ -644,30 +726,15 @@ __device__ void narrow_unit(const DevPool& P, const AttnLaunch& A, const AttnUni
       qk_direct<FP8, RB>(t, qq, s0, s1);
     }
   };
-  const float sl = A.scale_log2;
-
-  auto fetch_k = [&](const TileMeta& m, Tile<FP8>& t) {
-    load_k<FP8>(P.k_cache + head_off<FP8>(m.b0, P.Hkv, U.kvh), P.k_cache + head_off<FP8>(m.b1, P.Hkv, U.kvh), g,
-                lane, t);
-  };
-  auto fetch_v = [&](const TileMeta& m, Tile<FP8>& t) {
-    load_v<FP8>(P.v_cache + head_off<FP8>(m.b0, P.Hkv, U.kvh), P.v_cache + head_off<FP8>(m.b1, P.Hkv, U.kvh), g, t);
-  };
-  auto meta = [&](int i, TileMeta& m) { ids.tile(i, m.b0, m.b1, m.ks0, m.ks1, m.vs0, m.vs1); };
-  Tile<FP8> ta, tb;
-  TileMeta ma{}, mb{}, na{}, nb{};  // current and next (tile + 2) metadata of buffers A and B
-  if (U.nblk < 0) __builtin_amdgcn_s_waitcnt(0);  // the appended token is in the cache
-  meta(0, ma);
-  fetch_k(ma, ta);
-  fetch_v(ma, ta);
-  if (ntile > 1) {
-    meta(1, mb);
-    fetch_k(mb, tb);
-    fetch_v(mb, tb);
+  if constexpr (FP8) {
+    ids.first_scales();
+    meta(0, ma);
+    if (ntile > 1) meta(1, mb);
   }
   f32x4 s0[RB], s1[RB];
   scores(ta, s0, s1);
   if (ntile > 2) {
+    if (open) __builtin_amdgcn_s_waitcnt(0);  // the appended token is in the cache before its tile is read
     meta(2, na);
     fetch_k(na, ta);
   }
@@ -696,7 +763,7 @@ __device__ void narrow_unit(const DevPool& P, const AttnLaunch& A, const AttnUni
     if (i + 1 < ntile) step(i + 1, tb, mb, nb, ta, na);
   }
 #pragma unroll
-  for (int r = 0; r < RB; ++r) write_partial(P, A, U, 16 * r, R, g.q, g.lr, st[r]);
+  for (int r = 0; r < RB; ++r) write_partial(A, U, qrow[r], g.q, st[r]);
 }
 
 // ----------------------------------------------------------- cooperative --
@@ -770,22 +837,17 @@ __device__ void coop_unit(const DevPool& P, const AttnLaunch& A, const AttnUnit&
   constexpr int ring = FP8 ? kRing8 : kRing, ahead = FP8 ? kAhead8 : kAhead;
   constexpr int stage = FP8 ? kStage8 : kStage;
   const int32_t* brow = P.table + (size_t)U.owner * P.max_blocks + U.jb0;
-  // a cooperative item is a shared run: its end is in the plan
-  const int ntok = U.nblk >= 0 ? U.nblk * kBlock : P.seq_len[U.owner] + A.len_bias - U.jb0 * kBlock;
+  const int ntok = U.nblk * kBlock;  // a cooperative item is a shared run: its end is in the plan
   if (ntok <= 0) return;  // uniform over the workgroup
-  const int R = U.mem_cnt * P.g;  // <= 64 RB
+  const int R = U.mem_cnt << A.gshift;  // <= 64 RB
   const LaneGeom g = lane_geom(lane);
-  const int nblk = (ntok + kBlock - 1) / kBlock;
+  const int nblk = U.nblk;
   const int ntile = (ntok + 31) / 32;
   const int row0 = 16 * RB * wave;
   const bool active = row0 < R;
+  int qrow[RB];
   bf16x8 qf[RB][4];
   RowState st[RB];
-#pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    load_q(P, A, U, row0 + 16 * r, R, FP8, g.q, g.lr, qf[r]);
-    row_init(st[r]);
-  }
   const float sl = A.scale_log2;
   // lane's operand offsets in a stage
   const int koff = FP8 ? (g.kb1 ? kK1_8 : 0) + g.q * 256 + (lane & 7) * 16
@@ -866,12 +928,7 @@ __device__ void coop_unit(const DevPool& P, const AttnLaunch& A, const AttnUnit&
   auto fetch_ids = [&](int w) {
     if (wave == 0) dma4(brow + min(64 * w + lane, nblk - 1), idw + 64 * (w & 1));
   };
-  auto issue = [&](int i) {
-    const int j0 = 2 * i;
-    if ((j0 & 63) == 0 && j0 > 0) fetch_ids((j0 >> 6) + 1);
-    const int2 pr = *reinterpret_cast<const int2*>(idw + 64 * ((j0 >> 6) & 1) + (j0 & 63));
-    int b0 = __builtin_amdgcn_readfirstlane(pr.x);
-    int b1 = j0 + 1 < nblk ? __builtin_amdgcn_readfirstlane(pr.y) : b0;
+  auto move = [&](int i, int b0, int b1) {
     if ((unsigned)b0 >= (unsigned)P.num_blocks || (unsigned)b1 >= (unsigned)P.num_blocks) {
       if (t == 0) atomicOr(P.err, kErrBadBlock);
       b0 = (unsigned)b0 < (unsigned)P.num_blocks ? b0 : 0;
@@ -900,6 +957,13 @@ __device__ void coop_unit(const DevPool& P, const AttnLaunch& A, const AttnUnit&
       dma16(P.v_cache + o, stg + kV8 + wave * 1024);
     }
   };
+  auto issue = [&](int i) {
+    const int j0 = 2 * i;
+    if ((j0 & 63) == 0 && j0 > 0) fetch_ids((j0 >> 6) + 1);
+    const int2 pr = *reinterpret_cast<const int2*>(idw + 64 * ((j0 >> 6) & 1) + (j0 & 63));
+    const int b0 = __builtin_amdgcn_readfirstlane(pr.x);
+    move(i, b0, j0 + 1 < nblk ? __builtin_amdgcn_readfirstlane(pr.y) : b0);
+  };
   // Waits until this wave's loads of the tiles before the `later` last
   // issued ones are in LDS (wave 0 issues one more load per fp8 tile).
   auto wait = [&](int later) {
@@ -910,13 +974,21 @@ __device__ void coop_unit(const DevPool& P, const AttnLaunch& A, const AttnUnit&
     else
       wait_tiles_per<2>(later);
   };
+  // The first two tiles (their ids are in the unit), the first id windows
+  // and the queries travel together; the ring's other tiles follow.
+  move(0, U.first[0], nblk > 1 ? U.first[1] : U.first[0]);
+  if (ntile > 1) move(1, U.first[2], nblk > 3 ? U.first[3] : U.first[2]);
   fetch_ids(0);
   if (nblk > 64) fetch_ids(1);
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // Q operands and the first id windows are in
+#pragma unroll
+  for (int r = 0; r < RB; ++r) {
+    qrow[r] = query_row(A, U, P.Hq, row0 + 16 * r, R, g.lr);
+    load_q(A, qrow[r], FP8, g.q, qf[r]);
+    row_init(st[r]);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // all of them are in
   barrier_no_fence();
-  for (int i = 0; i < ahead && i < ntile; ++i) issue(i);
-  wait(min(ahead, ntile) - 1);  // tile 0 is in LDS
-  barrier_no_fence();
+  for (int i = 2; i < ahead && i < ntile; ++i) issue(i);
   f32x4 s0[RB], s1[RB];
   if (active) qk(lds, s0, s1);
   // Iteration i issues the scores of tile i + 1 before the softmax and P.V
@@ -941,25 +1013,25 @@ __device__ void coop_unit(const DevPool& P, const AttnLaunch& A, const AttnUnit&
   }
   if (active) {
 #pragma unroll
-    for (int r = 0; r < RB; ++r) write_partial(P, A, U, row0 + 16 * r, R, g.q, g.lr, st[r]);
+    for (int r = 0; r < RB; ++r) write_partial(A, U, qrow[r], g.q, st[r]);
   }
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs, so workgroup bid
 // runs on XCD bid % 8.  The plan lists every XCD's workgroup slots
-// contiguously, four entries per slot: a cooperative item (flagged in its
-// first entry) or four narrow units, in the order they should start
-// (longest first).  Cooperative (compute-bound) and narrow (HBM-bound)
-// slots are interleaved so both kinds share every CU.  Workgroup j of an
-// XCD runs slot j, except in the XCD's last kTailSlots slots: those are
-// claimed at run time, from the front by the XCD's own workgroups and from
-// the back (the shortest slots) by workgroups of XCDs that have no work
-// left, so the XCDs finish together.  One atomic word per XCD holds both
-// claim counts (front in the low half), so front and back claims never
-// meet; there are at least as many workgroups as slots.
-
-__device__ inline int tail_start(const AttnLaunch& A, int x) {
-  return max((A.xcd_off[x + 1] - A.xcd_off[x]) / kUnitsPerWG - kTailSlots, 0);
+// contiguously, four entries per slot: a cooperative item (flagged in every
+// entry) or four narrow units, in the order they should start (longest
+// first).  Cooperative (compute-bound) and narrow (HBM-bound) slots are
+// interleaved so both kinds share every CU.  Workgroup j of an XCD runs slot
+// j, except past the XCD's static slots (static_slots: all but the last
+// kTailSlots, and at least the ones that start together): those are claimed
+// at run time, from the front by the XCD's own workgroups and from the back
+// (the shortest slots) by workgroups of XCDs that have no work left, so the
+// XCDs finish together.  One atomic word per XCD holds both claim counts
+// (front in the low half), so front and back claims never meet; there are at
+// least as many workgroups as slots.
+__device__ inline int xcd_slots(const AttnLaunch& A, int x) {
+  return (A.xcd_off[x + 1] - A.xcd_off[x]) / kUnitsPerWG;
 }
 
 template <bool FP8>
@@ -967,42 +1039,40 @@ __global__ __launch_bounds__(kThreads, 2) void attn_units_kernel(DevPool P, Attn
   __shared__ __attribute__((aligned(16))) uint8_t lds[(FP8 ? kRing8 * kStage8 : kRing * kStage) + kIdsBytes];
   static_assert(!FP8 || 4 * 8192 <= kRing8 * kStage8, "narrow waves' Q regions (two row blocks)");
   __shared__ int claimed;
-  if (threadIdx.x == 0) {
-    const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
-    int b = -1;
-    if (j < tail_start(A, x)) {
-      b = A.xcd_off[x] + kUnitsPerWG * j;
-    } else {
+  const int bid = __builtin_amdgcn_workgroup_id_x(), x = bid & 7, j = bid >> 3;
+  int base = A.xcd_off[x] + kUnitsPerWG * j;
+  if (j >= static_slots(xcd_slots(A, x), A.resident)) {
+    if (threadIdx.x == 0) {
+      int b = -1;
       for (int k = 0; k < 8 && b < 0; ++k) {
         const int y = (x + k) & 7;
-        const int s0 = tail_start(A, y);
-        const int m = (A.xcd_off[y + 1] - A.xcd_off[y]) / kUnitsPerWG - s0;
+        const int ns = xcd_slots(A, y), s0 = static_slots(ns, A.resident);
+        const int m = ns - s0;
         if (m <= 0) continue;
         const unsigned old = atomicAdd(reinterpret_cast<unsigned*>(A.queues) + y, k == 0 ? 1u : 0x10000u);
         const int f = (int)(old & 0xffffu), bk = (int)(old >> 16);
         if (f + bk < m) b = A.xcd_off[y] + kUnitsPerWG * (s0 + (k == 0 ? f : m - 1 - bk));
       }
+      claimed = b;
     }
-    claimed = b;
+    __syncthreads();
+    base = __builtin_amdgcn_readfirstlane(claimed);
+    if (base < 0) return;  // uniform over the workgroup
   }
-  __syncthreads();
-  const int base = claimed;
-  if (base < 0) return;  // uniform over the workgroup
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const AttnUnit U0 = A.units[base];
-  if (U0.flags & kUnitCoop) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const AttnUnit U = load_unit(A.units + base + wave);  // a slot always has four entries
+  if (U.flags & kUnitCoop) {
     // up to 64 rows: one row block per wave; more: two
-    if (U0.mem_cnt * P.g > 4 * kRowsPerUnit)
-      coop_unit<FP8, 2>(P, A, U0, wave, lane, lds);
-    else if (U0.mem_cnt > 0)
-      coop_unit<FP8, 1>(P, A, U0, wave, lane, lds);
+    if ((U.mem_cnt << A.gshift) > 4 * kRowsPerUnit)
+      coop_unit<FP8, 2>(P, A, U, wave, lane, lds);
+    else if (U.mem_cnt > 0)
+      coop_unit<FP8, 1>(P, A, U, wave, lane, lds);
     return;
   }
-  const AttnUnit U = A.units[base + wave];  // a narrow slot always has four entries
   // no barrier on the narrow path; fp8 units of 17-32 rows take two row
   // blocks in one wave
   if constexpr (FP8) {
-    if (U.mem_cnt * P.g > kRowsPerUnit)
+    if ((U.mem_cnt << A.gshift) > kRowsPerUnit)
       narrow_unit<FP8, 2>(P, A, U, lane, lds + wave * 8192);
     else if (U.mem_cnt > 0)
       narrow_unit<FP8, 1>(P, A, U, lane, nullptr);

@@ -49,6 +49,11 @@ constexpr double kUsNarrow8 = 0.045;     // fp8, <= 16 rows
 constexpr double kUsNarrowTwo8 = 0.055;  // fp8, 17-32 rows (two row blocks)
 constexpr double kUsCoop16 = 0.042;     // bf16, any row count
 constexpr double kUsCoop64_8 = 0.037, kUsCoop128_8 = 0.051;  // fp8, 33-64 and 65-128 rows
+// The same while launches are balanced, for the order in which slots start
+// (bf16; fp8 uses the times above): per-wave timelines give 0.09-0.10 for
+// narrow units and 0.04 / 0.05 for cooperative items of up to 64 / 128 rows,
+// which are taken 1.25 times.
+constexpr double kStartNarrow16 = 0.09, kStartCoop64_16 = 0.05, kStartCoop128_16 = 0.064;
 // Chunk caps as fractions of the estimated launch length.
 constexpr double kCapNarrow = 1.0, kCapCoop = 0.5;
 
@@ -96,7 +101,7 @@ bool layout_of(const gambit_pool_desc* d, Layout* L) {
   L->freebits = take(4 * (size_t)L->nwords);
   L->alloc_list = take(4 * (size_t)d->num_blocks);
   L->units = take(sizeof(AttnUnit) * (size_t)L->max_units);
-  L->members = take(4 * (size_t)L->max_members);
+  L->members = take(4 * ((size_t)L->max_members + gambit::kMemberPad));
   L->part_ml = take(8 * (size_t)T * d->num_q_heads * kmax);
   L->part_acc = take(4 * (size_t)T * d->num_q_heads * kmax * gambit::kHeadDim);
   L->sbar = take(4 * (size_t)T);
@@ -142,6 +147,7 @@ struct gambit_pool {
   bool plan_valid = false;
   std::vector<int32_t> plan_list;
   int xcd_off[9] = {0};
+  int plan_steps = 0;              // decode steps taken with the plan
   int grid = 0;
   int n_units = 0;
   bool queues_dirty = false;       // an attention launch was not followed by its merge
@@ -327,6 +333,9 @@ gambit_status check_ids(gambit_pool* p, int32_t n, const int32_t* ids, const cha
 }
 
 // ---- planner ---------------------------------------------------------------
+// Attention workgroups one XCD runs at once (two per compute unit, 8 XCDs).
+int attn_resident(const gambit_pool* p) { return std::max(1, 2 * p->n_cu / 8); }
+
 // Cuts every listed trace's context into runs of blocks referenced by the
 // same set of listed traces.  Sharing only ever comes from forks, which hand
 // the child the parent's whole full-block prefix, so along one trace the set
@@ -488,11 +497,23 @@ gambit_status build_plan(gambit_pool* p, int n, const int32_t* ids, hipStream_t 
                     int kidx) {
       const int moff = (int)members.size();
       members.insert(members.end(), mem_ids, mem_ids + mcnt);
+      AttnUnit u{ids[owner_pos], jb0, nblk, 0, moff, mcnt, kidx, 0, {0, 0, 0, 0}, {-1, -1, -1, -1}};
+      const auto& orow = p->table[ids[owner_pos]];
+      for (int k = 0; k < 4 && jb0 + k < (nblk < 0 ? (int)orow.size() : jb0 + nblk); ++k) u.first[k] = orow[jb0 + k];
+      auto unit = [&](int h, int m0, int mc, int flags) {
+        u.kvh = h;
+        u.mem_off = moff + m0;
+        u.mem_cnt = mc;
+        u.flags = flags;
+        for (int k = 0; k < 4; ++k) u.pos[k] = k < mc ? mem_ids[m0 + k] : 0;
+        if (nblk < 0) u.pos[1] = p->seq_len[ids[owner_pos]];
+        return u;
+      };
       const double tok = std::max(ntok_est, 1);
       if (mcnt * p->g <= narrow_rows) {
         for (int h = 0; h < Hkv; ++h) {
           groups.push_back(Group{tok, (int32_t)gunits.size(), 1, false});
-          gunits.push_back(AttnUnit{ids[owner_pos], jb0, nblk, h, moff, mcnt, kidx, 0});
+          gunits.push_back(unit(h, 0, mcnt, 0));
         }
         return;
       }
@@ -501,7 +522,7 @@ gambit_status build_plan(gambit_pool* p, int n, const int32_t* ids, hipStream_t 
         Group gr{0.0, (int32_t)gunits.size(), 0, true};
         for (int m0 = 0; m0 < mcnt; m0 += item_members) {
           const int mc = std::min(item_members, mcnt - m0);
-          gunits.push_back(AttnUnit{ids[owner_pos], jb0, nblk, h, moff + m0, mc, kidx, gambit::kUnitCoop});
+          gunits.push_back(unit(h, m0, mc, gambit::kUnitCoop));
           ++gr.count;
           gr.cost += tok * (2.0 + 4.0 * mc * p->g / 64.0);  // staging + compute per row
         }
@@ -574,39 +595,51 @@ gambit_status build_plan(gambit_pool* p, int n, const int32_t* ids, hipStream_t 
     per[x].push_back(gi);
   }
   // Workgroup slots of four entries per XCD: a cooperative item (repeated
-  // four times, flagged) or four narrow units.  The two kinds are interleaved
-  // in proportion so compute-bound and HBM-bound workgroups share every CU,
-  // the cooperative items over the first part of the narrow slots: they are
-  // the long ones, and one that starts late ends the launch late.  bf16
-  // (bound by HBM): over the first 85% (853 vs 858 us at 512 traces with all
-  // of them; 50% starts too few narrow units early there: 947 vs 936-939 us,
-  // though at 256 traces it gives 268 vs 273 us).
-  // fp8 (bound by instruction issue, where the cooperative items' share of
-  // the work starting early matters more than the overlap): over the first
-  // 50% (217-220 vs 233-241 us at 256 traces; 45%: 226, 55%: 228, 70%: 224).
-  const long spread_pct = p->d.kv_dtype == GAMBIT_KV_FP8_E4M3 ? 50 : 85;
+  // four times, flagged) or four narrow units, in the order they start: the
+  // longest first (start_us, tokens times the kind's time), so that no long
+  // one starts late and ends the launch by itself; the one-tile units of
+  // freshly branched traces, a quarter of all slots right after a round, come
+  // last.  Against cooperative items spread over the first 50% (fp8) or 85%
+  // (bf16) of the narrow slots by count, per pass of 16 steps: 256 traces fp8
+  // 3716 -> 3597 us, 512 traces 15024 -> 14661 us, 256 private traces 9218 ->
+  // 9151 us, six layers of 45 traces 1688 -> 1591 us, 64 traces 1519 ->
+  // 1530 us.  bf16 weighs cooperative items 1.25 times their time (HBM-bound
+  // units beside them from early on): 1.0 gives 14681 and 9294 us, 1.5 14594
+  // and 9288 us; fp8 (bound by instruction issue) at 1.5: 3880 us.
   std::vector<AttnUnit> units;
   units.reserve(4 * gunits.size() + 8 * gambit::kUnitsPerWG);  // a cooperative item fills a 4-entry slot
-  const AttnUnit empty{0, 0, 0, 0, 0, 0, 0, 0};
-  std::vector<AttnUnit> C, N;
+  const AttnUnit empty{};
+  auto start_us = [&](const AttnUnit& u) {
+    const double tok = u.nblk >= 0 ? 16.0 * u.nblk : (double)(u.pos[1] - 16 * u.jb0);
+    const int rows = u.mem_cnt * p->g;
+    if (fp8) return tok * unit_us(rows);
+    return tok * (rows <= narrow_rows ? kStartNarrow16 : rows <= 4 * gambit::kRowsPerUnit ? kStartCoop64_16 : kStartCoop128_16);
+  };
+  std::vector<std::pair<double, int32_t>> C;  // (time, unit) of the XCD's cooperative items
+  std::vector<int32_t> N;                     // its narrow units, most tokens first
   for (int x = 0; x < 8; ++x) {
     p->xcd_off[x] = (int)units.size();
     C.clear();
     N.clear();
     for (int gi : per[x]) {
       const Group& g = groups[gi];
-      (g.coop ? C : N).insert((g.coop ? C : N).end(), gunits.begin() + g.first, gunits.begin() + g.first + g.count);
+      for (int k = g.first; k < g.first + g.count; ++k) {
+        if (g.coop)
+          C.emplace_back(start_us(gunits[k]), k);
+        else
+          N.push_back(k);
+      }
     }
-    const long nC = (long)C.size(), nN = cdiv((int)N.size(), gambit::kUnitsPerWG);
-    long ci = 0, ni = 0;
-    while (ci < nC || ni < nN) {
-      if (ni >= nN || (ci < nC && ci * std::max(1L, nN * spread_pct / 100) <= ni * nC)) {
-        for (int w = 0; w < gambit::kUnitsPerWG; ++w) units.push_back(C[ci]);
+    std::stable_sort(C.begin(), C.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+    const size_t nN = cdiv((int)N.size(), gambit::kUnitsPerWG);
+    for (size_t ci = 0, ni = 0; ci < C.size() || ni < nN;) {
+      if (ni >= nN || (ci < C.size() && C[ci].first >= start_us(gunits[N[ni * gambit::kUnitsPerWG]]))) {
+        for (int w = 0; w < gambit::kUnitsPerWG; ++w) units.push_back(gunits[C[ci].second]);
         ++ci;
       } else {
         for (int w = 0; w < gambit::kUnitsPerWG; ++w) {
-          const size_t k = (size_t)ni * gambit::kUnitsPerWG + w;
-          units.push_back(k < N.size() ? N[k] : empty);
+          const size_t k = ni * gambit::kUnitsPerWG + w;
+          units.push_back(k < N.size() ? gunits[N[k]] : empty);
         }
         ++ni;
       }
@@ -615,20 +648,20 @@ gambit_status build_plan(gambit_pool* p, int n, const int32_t* ids, hipStream_t 
   p->xcd_off[8] = (int)units.size();
   // one workgroup per slot, and at least as many per XCD as that XCD has
   // slots outside its run-time claimed tail
+  const int resident = attn_resident(p);
   int per_xcd = cdiv((int)units.size() / gambit::kUnitsPerWG, 8);
   for (int x = 0; x < 8; ++x)
-    per_xcd = std::max(per_xcd, (p->xcd_off[x + 1] - p->xcd_off[x]) / gambit::kUnitsPerWG - gambit::kTailSlots);
+    per_xcd = std::max(per_xcd, gambit::static_slots((p->xcd_off[x + 1] - p->xcd_off[x]) / gambit::kUnitsPerWG, resident));
   p->grid = 8 * per_xcd;
   p->n_units = (int)units.size();
   if ((int)units.size() > p->L.max_units || (int)members.size() > p->L.max_members)
     return fail(p, GAMBIT_ERR_UNSUPPORTED, "plan exceeds workspace bounds");
   // The kinds of work covering each list position, as the kernel will pick
-  // them (gambit_plan_kinds): a slot in an XCD's last kTailSlots is claimed
-  // at run time.
+  // them (gambit_plan_kinds): a slot in an XCD's tail is claimed at run time.
   p->plan_kinds.assign(n, 0);
   for (int x = 0; x < 8; ++x) {
     const int nslots = (p->xcd_off[x + 1] - p->xcd_off[x]) / gambit::kUnitsPerWG;
-    const int tail0 = std::max(nslots - gambit::kTailSlots, 0);
+    const int tail0 = gambit::static_slots(nslots, resident);
     for (int j = 0; j < nslots; ++j) {
       const int base = p->xcd_off[x] + gambit::kUnitsPerWG * j;
       const int32_t tail = j >= tail0 ? GAMBIT_UNIT_TAIL_SLOT : 0;
@@ -668,6 +701,7 @@ gambit_status build_plan(gambit_pool* p, int n, const int32_t* ids, hipStream_t 
   HIP_TRY(p, hipEventRecord(p->plan_ev, s), "plan fence");
   p->plan_list.assign(ids, ids + n);
   p->plan_valid = true;
+  p->plan_steps = 0;
   p->stats.n_units = p->n_units;
   p->stats.max_splits_used = p->max_splits_used;
   return GAMBIT_OK;
@@ -973,6 +1007,7 @@ static gambit_status decode_layer(gambit_pool* p, int32_t layer, int32_t n, cons
     if (!in_args)
       HIP_TRY(p, gambit::launch_alloc(p->dev, dlist, nullptr, 1, n, p->append_scale, true, s), "append alloc");
     A.list = dlist;
+    A.delta = ++p->plan_steps;
     A.len_bias = in_args ? 1 : 0;
     A.new_scale = p->append_scale;
     for (int i = 0; i < n; ++i) {
@@ -993,6 +1028,8 @@ static gambit_status decode_layer(gambit_pool* p, int32_t layer, int32_t n, cons
     A.part_acc = ws_ptr<float>(p, p->L.part_acc);
     A.part_ml = ws_ptr<float2>(p, p->L.part_ml);
     A.kmax = p->L.kmax;
+    A.gshift = __builtin_ctz(p->g);
+    A.resident = attn_resident(p);
     A.n = n;
     p->stats.total_tokens += n;
     p->stats.unique_tokens += n;

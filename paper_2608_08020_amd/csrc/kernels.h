@@ -34,8 +34,15 @@ struct AttnUnit {
   int32_t mem_off;  // first member (list position) in the member array
   int32_t mem_cnt;  // members in this tile; 0 = padding unit (does nothing)
   int32_t kidx;     // partial slot of this run for every member
-  int32_t flags;    // kUnitCoop in the first entry of a cooperative workgroup slot
+  int32_t flags;    // kUnitCoop in every entry of a cooperative workgroup slot
+  // What a wave needs before its first cache load, so that the entry (one
+  // 64-byte scalar load) is the only thing it waits for.
+  int32_t pos[4];   // list positions of the first four members; an open unit (nblk < 0, one
+                    //   member) holds its owner's length at plan time in pos[1]
+  int32_t first[4]; // ids of the run's first four blocks as the plan saw them, -1 = not there yet
 };
+static_assert(sizeof(AttnUnit) == 64, "one scalar load");
+constexpr int kMemberPad = 4;  // readable entries past the members (scalar loads of four)
 
 enum : int32_t { kUnitCoop = 1 };
 
@@ -44,6 +51,13 @@ enum : int32_t { kUnitCoop = 1 };
 constexpr int kRowsPerNarrowFp8 = 32;
 constexpr int kRowsPerCoop = 128;  // rows of one cooperative item (4 waves x up to 2 row blocks)
 constexpr int kTailSlots = 96;     // last workgroup slots of an XCD, claimed at run time
+// Of an XCD's n slots, the first static_slots(n, r) belong to its workgroups
+// by index, the rest are claimed at run time; r slots are resident at once.
+// The first r all start together, so claiming them could move nothing.
+__host__ __device__ inline int static_slots(int n, int resident) {
+  const int a = n - kTailSlots, b = n < resident ? n : resident;
+  return a > b ? a : b;
+}
 
 // Device view of a pool.
 struct DevPool {
@@ -101,6 +115,9 @@ struct AttnLaunch {
   float* part_acc;          // [n][Hq][kmax][128]
   float2* part_ml;          // [n][Hq][kmax] (running max in log2 units, sum)
   int32_t kmax;
+  int32_t gshift;           // log2 of the GQA group
+  int32_t resident;         // workgroup slots an XCD runs at once
+  int32_t delta;            // tokens each listed trace has taken since the plan, this step's included
   int32_t n;
   float scale_log2;         // sm_scale * log2(e)
   void* out;

@@ -21,7 +21,7 @@ __host__ __device__ constexpr int seq_kstride(int max_steps) { return (max_steps
 __host__ __device__ constexpr size_t seq_region_floats(int max_steps) {
   return (size_t)2 * 64 * seq_kstride(max_steps) + 64;
 }
-enum : int { kEpiNone = 0, kEpiSwiGLU = 1 };
+enum : int { kEpiNone = 0, kEpiSwiGLU = 1, kEpiAdd = 2 };
 
 struct SeqDev {
   const int32_t* ids;     // [n] listed trace slots, this boundary
@@ -35,27 +35,30 @@ struct SeqDev {
   int32_t d_model, n_heads, n_layers, max_steps;
 };
 
-// C = A W^T (fp32); N a multiple of 64, K / splits a multiple of 16.
-// part != NULL: the raw sums of the splits go to part[splits][M][N] (for
-// seq_reduce_ln); else one split, written to C as it is (kEpiNone) or
-// through the SwiGLU gate (kEpiSwiGLU).
-hipError_t seq_gemm(const float* A, const float* W, float* C, int M, int N, int K, int splits, int epi, float* part,
-                    hipStream_t s);
+// fp32 products with W [N][K] row-major, K a multiple of 64:
+//   seq_gemm_ln         C = LN(A; lg, lb) W^T, N a multiple of 192 (QKV)
+//   seq_gemm_ln_swiglu  C[M][N / 2] = SiLU(a1) * a3 of a = LN(A) W^T, N a
+//                       multiple of 128, W_1 and W_3 rows interleaved by 16
+//   seq_gemm_add        C += A W^T, N a multiple of 64
+// stats [M][columns / 16]: (mean, sum of squared deviations) of every 16
+// columns of a row of x, written with x (seq_reduce_in, seq_gemm_add) and
+// read by the products that normalise it.
+hipError_t seq_gemm_ln(const float* A, const float* W, float* C, int M, int N, int K, const float* lg, const float* lb,
+                       const float2* stats, hipStream_t s);
+hipError_t seq_gemm_ln_swiglu(const float* A, const float* W, float* C, int M, int N, int K, const float* lg,
+                              const float* lb, const float2* stats, hipStream_t s);
+hipError_t seq_gemm_add(const float* A, const float* W, float* C, int M, int N, int K, float2* stats, hipStream_t s);
 // The input projection's bf16 planes [3][dm][dim] of W_in scaled by the
 // input LayerNorm's gain (hi + mid + lo equal it exactly), their row sums c
 // and dv = W_in b (one launch, at creation).
 hipError_t seq_prep_input(const float* w_in, const float* ln_g, const float* ln_b, int dim, int dm, uint16_t* planes,
                           float* c, float* dv, hipStream_t s);
 // x = GELU(LN_in(h) W_in^T) from the split partial sums of h against the
-// planes (part [splits][n][3 d]), then as seq_reduce_ln.
+// planes (part [splits][n][3 d]).
 hipError_t seq_reduce_in(const uint16_t* h, int dim, const float* part, int splits, const float* c, const float* dv,
-                         float* x, int d, const float* g, const float* b, float* u, bool head, const SeqDev& S,
-                         float* scores, int n, hipStream_t s);
-// x = R + the sum of the splits of part (R, the residual, may be x itself),
-// then u = LN(x; g, b), or with head the output head's scores and the step
-// counts' advance.
-hipError_t seq_reduce_ln(const float* part, int splits, const float* R, float* x, int d, const float* g,
-                         const float* b, float* u, bool head, const SeqDev& S, float* scores, int n, hipStream_t s);
+                         float* x, int d, float2* stats, int n, hipStream_t s);
+// The output head's scores from x, and the step counts' advance.
+hipError_t seq_head(const float* x, int d, const SeqDev& S, float* scores, int n, hipStream_t s);
 // parts[s][t][u] = the sum over split s's k range of h[t][k] w[u][k], bf16
 // operands and fp32 sums, for s < splits: the MLP scorer's split-k GEMM
 // without its epilogue (mlp_scorer.hip).  dim a multiple of 128, units a

@@ -19,8 +19,7 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct SeqLayout {
-  size_t ids, pairs, lens, err, cache, planes, cvec, dvec, part, x, u, qkv, o, g, total;
-  int out_splits;  // of the d_model-wide projections (W_o, W_2) over their K
+  size_t ids, pairs, lens, err, cache, planes, cvec, dvec, part, x, stats, qkv, o, g, total;
 };
 
 bool seq_layout(const gambit_scorer_desc* d, SeqLayout* L) {
@@ -31,11 +30,6 @@ bool seq_layout(const gambit_scorer_desc* d, SeqLayout* L) {
   if (d->input_dim % 128 || d->d_ff % 64) return false;         // GEMM tiles
   if (d->max_steps > 8192) return false;                        // LDS of the attention step
   const size_t T = d->max_traces, D = d->input_dim, dm = d->d_model, f = d->d_ff;
-  // W_o (K = d_model) and W_2 (K = d_ff) have d_model / 64 column tiles:
-  // split their K four ways (while the parts stay >= 64 deep) to fill the GPU
-  L->out_splits = 4;
-  while (L->out_splits > 1 && (dm % (64 * (size_t)L->out_splits) || f % (64 * (size_t)L->out_splits)))
-    --L->out_splits;
   size_t o = 0;
   auto take = [&](size_t bytes) {
     const size_t at = o;
@@ -50,14 +44,14 @@ bool seq_layout(const gambit_scorer_desc* d, SeqLayout* L) {
   L->planes = take(2 * 3 * dm * D);
   L->cvec = take(4 * dm);
   L->dvec = take(4 * dm);
-  // split partial sums: the input projection's (splits x n x 3 d_model, the
-  // largest over every n <= max_traces) or W_o's and W_2's
-  size_t part = (size_t)L->out_splits * T * dm;
+  // the input projection's split partial sums (splits x n x 3 d_model), the
+  // largest over every n <= max_traces
+  size_t part = 0;
   for (size_t n = 1; n <= T; ++n)
     part = std::max(part, (size_t)gambit::bf16_partial_splits((int)n, (int)D, (int)(3 * dm)) * n * 3 * dm);
   L->part = take(4 * part);
   L->x = take(4 * T * dm);
-  L->u = take(4 * T * dm);
+  L->stats = take(8 * T * (dm / 16));
   L->qkv = take(4 * T * 3 * dm);
   L->o = take(4 * T * dm);
   L->g = take(4 * T * f);
@@ -225,7 +219,7 @@ gambit_status gambit_scorer_step(gambit_scorer* q, int32_t n, const int32_t* ids
   const int D = d.input_dim, dm = d.d_model, f = d.d_ff;
   float* part = wsp<float>(q, q->L.part);
   float* x = wsp<float>(q, q->L.x);
-  float* u = wsp<float>(q, q->L.u);
+  float2* stats = wsp<float2>(q, q->L.stats);
   float* qkv = wsp<float>(q, q->L.qkv);
   float* o = wsp<float>(q, q->L.o);
   float* g = wsp<float>(q, q->L.g);
@@ -234,38 +228,21 @@ gambit_status gambit_scorer_step(gambit_scorer* q, int32_t n, const int32_t* ids
   const int in_splits = bf16_partial_splits(n, D, 3 * dm);
   SEQ_TRY(q, bf16_gemm_partials(hb, wsp<uint16_t>(q, q->L.planes), n, D, 3 * dm, in_splits, part, s),
           "input projection");
-  // each K-split projection's reduce also takes the LayerNorm after it: LN1
-  // of the next layer, LN2, or LN_out with the head after the last layer
-  {
-    const bool head = d.n_layers == 0;
-    SEQ_TRY(q, seq_reduce_in(hb, D, part, in_splits, wsp<float>(q, q->L.cvec), wsp<float>(q, q->L.dvec), x, dm,
-                             head ? nullptr : d.ln1_g, head ? nullptr : d.ln1_b, u, head, q->dev, scores_out, n, s),
-            "input projection reduce");
-  }
-  auto reduce_ln = [&](int splits, const float* R, int next_ln1, const char* where) -> gambit_status {
-    const bool head = next_ln1 >= d.n_layers;
-    const float* g = head ? nullptr : d.ln1_g + (size_t)next_ln1 * dm;
-    const float* b = head ? nullptr : d.ln1_b + (size_t)next_ln1 * dm;
-    SEQ_TRY(q, seq_reduce_ln(part, splits, R, x, dm, g, b, u, head, q->dev, scores_out, n, s), where);
-    return GAMBIT_OK;
-  };
+  SEQ_TRY(q, seq_reduce_in(hb, D, part, in_splits, wsp<float>(q, q->L.cvec), wsp<float>(q, q->L.dvec), x, dm, stats,
+                           n, s),
+          "input projection reduce");
   for (int l = 0; l < d.n_layers; ++l) {
-    const size_t dd = (size_t)dm * dm;
-    SEQ_TRY(q, seq_gemm(u, d.w_qkv + 3 * dd * l, qkv, n, 3 * dm, dm, 1, kEpiNone, nullptr, s),
-            "QKV");
+    const size_t dd = (size_t)dm * dm, v = (size_t)l * dm;
+    SEQ_TRY(q, seq_gemm_ln(x, d.w_qkv + 3 * dd * l, qkv, n, 3 * dm, dm, d.ln1_g + v, d.ln1_b + v, stats, s),
+            "LN1, QKV");
     SEQ_TRY(q, seq_attention(q->dev, l, qkv, o, n, s), "attention step");
-    SEQ_TRY(q, seq_gemm(o, d.w_o + dd * l, x, n, dm, dm, q->L.out_splits, kEpiNone, part, s),
-            "output projection");
-    SEQ_TRY(q, seq_reduce_ln(part, q->L.out_splits, x, x, dm, d.ln2_g + (size_t)l * dm,
-                             d.ln2_b + (size_t)l * dm, u, false, q->dev, scores_out, n, s),
-            "output projection reduce, LN2");
-    SEQ_TRY(q, seq_gemm(u, d.w_13 + 2 * (size_t)f * dm * l, g, n, 2 * f, dm, 1, kEpiSwiGLU, nullptr, s),
-            "SwiGLU");
-    SEQ_TRY(q, seq_gemm(g, d.w_2 + (size_t)f * dm * l, x, n, dm, f, q->L.out_splits, kEpiNone, part, s),
-            "SwiGLU out");
-    st = reduce_ln(q->L.out_splits, x, l + 1, "SwiGLU out reduce, next LayerNorm");
-    if (st) return st;
+    SEQ_TRY(q, seq_gemm_add(o, d.w_o + dd * l, x, n, dm, dm, stats, s), "output projection");
+    SEQ_TRY(q, seq_gemm_ln_swiglu(x, d.w_13 + 2 * (size_t)f * dm * l, g, n, 2 * f, dm, d.ln2_g + v, d.ln2_b + v, stats,
+                                  s),
+            "LN2, SwiGLU");
+    SEQ_TRY(q, seq_gemm_add(g, d.w_2 + (size_t)f * dm * l, x, n, dm, f, stats, s), "SwiGLU out");
   }
+  SEQ_TRY(q, seq_head(x, dm, q->dev, scores_out, n, s), "output head");
   for (int i = 0; i < n; ++i) ++q->lens[ids[i]];
   return GAMBIT_OK;
 }

@@ -10,16 +10,16 @@
 //                                           planes, K split; mlp_scorer.hip);
 //                                           reduce_in_kernel (the splits and
 //                                           planes added, LN_in applied)
-//   per layer: u = LN1(x); qkv = u Wqkv^T; o = attention step (RoPE, append
-//   the step's key and value, attend over the trace's steps 0..t);
-//   x += o Wo^T; u = LN2(x); a = u W13^T; g = SiLU(a1) * a3; x += g W2^T
+//   per layer: qkv = LN1(x) Wqkv^T; o = attention step (RoPE, append the step's
+//   key and value, attend over the trace's steps 0..t); x += o Wo^T;
+//   g = SiLU(LN2(x) W1^T) * (LN2(x) W3^T); x += g W2^T
 //   y  = sigmoid(w_out . LN_out(x)), and the trace's step count advances.
-// A K-split projection's partial sums are added, its epilogue applied and the
-// LayerNorm that follows it (LN1, LN2, or LN_out and the head) taken in one
-// launch (reduce_ln_kernel, reduce_in_kernel): 16 launches per boundary with
+// Each product takes the LayerNorm before it on its operand's way in and the
+// residual or the gate on its result's way out: 13 launches per boundary with
 // two layers.
 #include <hip/hip_runtime.h>
 
+#include "lds_dma.h"
 #include "seq_kernels.h"
 
 namespace gambit {
@@ -56,130 +56,225 @@ __device__ inline float4 ld_stream4(const float* p) {
   return make_float4(v.x, v.y, v.z, v.w);
 }
 
-// C[M][N] = A[M][K] . W[N][K]^T over K range [z * ks, (z + 1) * ks) of split
-// z = blockIdx.z, on the fp32 matrix cores (v_mfma_f32_16x16x4f32).  TM x 64
-// tiles (TM = 64 or 32); the K range is taken in chunks of 128 that are
-// staged whole in LDS (rows padded to 132 floats, so the 16 rows of an
-// operand read fall on 16 different 16-byte bank groups), the next chunk's
-// global loads in flight in registers while the current one is multiplied.
-// Each of the 4 waves computes a (TM / 2) x 32 quarter as 16 x 16 products.
-// A lane reads 4 consecutive k of its row (one 16-byte read) and feeds them
-// to 4 successive products: lane (q, i) contributes A[i][4q + kk] and
-// W[i][4q + kk] to product kk, the same k for both operands, so each product
-// sums over k = 4q + kk, q = 0..3; result element (4 (l / 16) + r, l % 16)
-// sits in lane l, register r.
-// part != NULL: the raw sums of split z go
-// to part[z][M][N] for reduce_ln_kernel; else the epilogue is applied and C
-// written (one split).
-// kEpiSwiGLU: W holds W_1 and W_3 rows interleaved in groups of 16, so a
-// wave's two column blocks are W_1 and W_3 of the same 16 outputs, and
-// C[m][16 c + i] = SiLU(a1) * a3 with row stride N / 2.
-constexpr int kKC = 128;       // k per staged chunk
-constexpr int kKP = kKC + 4;   // padded LDS row, floats
-template <int TM>
-__global__ __launch_bounds__(256) void gemm_kernel(const float* A, const float* W, float* C, int M, int N, int K,
-                                                   int ks, int epi, float* part) {
-  constexpr int MB = TM / 32;                    // 16-row blocks per wave
-  constexpr int AV = TM * (kKC / 4) / 256;       // float4 groups of A per thread and chunk
-  constexpr int WV = 64 * (kKC / 4) / 256;       // of W
-  __shared__ __attribute__((aligned(16))) float As[TM * kKP];
-  __shared__ __attribute__((aligned(16))) float Ws[64 * kKP];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * 64;
-  const int k0 = blockIdx.z * ks;
-  const int li = lane & 15, lq = lane >> 4;
-  const int wm = (wave >> 1) * (TM / 2), wn = (wave & 1) * 32;
-  // loader: group g = tid + 256 v is row g / 32, k offset 4 (g % 32); the k
-  // offset is the same for every v
-  const int lk = 4 * (tid & 31), lr = tid >> 5;
-  float4 ar[AV], wr[WV];
-  // chunk [kb, kb + kn): groups past kn (a shorter last chunk) stay zero and
-  // read nothing
-  auto fetch = [&](int kb, int kn) {
-    const bool kin = lk < kn;
-#pragma unroll
-    for (int v = 0; v < AV; ++v) {
-      const int m = m0 + lr + 8 * v;
-      ar[v] = (m < M && kin) ? *reinterpret_cast<const float4*>(A + (size_t)m * K + kb + lk)
-                             : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int v = 0; v < WV; ++v)
-      wr[v] = kin ? *reinterpret_cast<const float4*>(W + (size_t)(n0 + lr + 8 * v) * K + kb + lk)
-                  : make_float4(0.f, 0.f, 0.f, 0.f);
-  };
-  f32x4 acc[MB][2];
-#pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  fetch(k0, min(kKC, ks));
-  for (int kb = k0; kb < k0 + ks; kb += kKC) {
-    const int kn = min(kKC, k0 + ks - kb);  // a multiple of 16
-    __syncthreads();  // the previous chunk's reads are done
-#pragma unroll
-    for (int v = 0; v < AV; ++v) *reinterpret_cast<float4*>(&As[(lr + 8 * v) * kKP + lk]) = ar[v];
-#pragma unroll
-    for (int v = 0; v < WV; ++v) *reinterpret_cast<float4*>(&Ws[(lr + 8 * v) * kKP + lk]) = wr[v];
-    __syncthreads();
-    if (kb + kKC < k0 + ks) fetch(kb + kKC, min(kKC, k0 + ks - kb - kKC));
-    for (int kc = 0; kc < kn; kc += 16) {
-      float4 a[MB], b[2];
-#pragma unroll
-      for (int i = 0; i < MB; ++i) a[i] = *reinterpret_cast<const float4*>(&As[(wm + 16 * i + li) * kKP + kc + 4 * lq]);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = *reinterpret_cast<const float4*>(&Ws[(wn + 16 * j + li) * kKP + kc + 4 * lq]);
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].x, b[j].x, acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].y, b[j].y, acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].z, b[j].z, acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].w, b[j].w, acc[i][j], 0, 0, 0);
-        }
-    }
-  }
-  if (epi == kEpiSwiGLU) {  // one split
-    const int f = N / 2, c = (n0 + wn) / 32;
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + 16 * i + 4 * lq + r;
-        if (m >= M) continue;
-        const float a = acc[i][0][r], b = acc[i][1][r];
-        C[(size_t)m * f + 16 * c + li] = a / (1.f + expf(-a)) * b;
-      }
-    return;
-  }
-  const bool split = part != nullptr;
-#pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + 16 * i + 4 * lq + r, n = n0 + wn + 16 * j + li;
-        if (m >= M) continue;
-        const size_t o = (size_t)m * N + n;
-        float v = acc[i][j][r];
-        if (split)
-          part[(size_t)blockIdx.z * M * N + o] = v;
-        else
-          C[o] = v;
-      }
+// Sum over the four lanes (l / 16) that hold a row of an operand.
+__device__ inline float row_sum(float v) {
+  v += __shfl_xor(v, 16);
+  return v + __shfl_xor(v, 32);
 }
 
-// One workgroup per row of a K-split projection (width d, a multiple of 64;
-// thread c takes columns c + 256 k): the splits' partial sums added in split
-// order (loaded eight splits at a time, indices clamped so all eight loads
-// are in flight together), the residual R added, the row x written; then
-// the LayerNorm of x (mean, then the mean squared deviation, each a fixed
-// reduction over the workgroup): head == 0 writes u = LN(x) with gain g,
-// bias b; head != 0 takes LN_out and the output head, scores[row] =
-// sigmoid(w_out . LN_out(x)), and advances the trace's step count.  Each
-// thread re-reads only the columns it wrote.
+// Sum over the 16 lanes of a lane group, in every lane, by data-parallel
+// moves (quad xor 1 and 2, half-row mirror, row mirror).
+template <int CTRL>
+__device__ inline float dpp_add(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+__device__ inline float group_sum(float v) {
+  v = dpp_add<0xB1>(v);
+  v = dpp_add<0x4E>(v);
+  v = dpp_add<0x141>(v);
+  return dpp_add<0x140>(v);
+}
+
+// (mean, sum of squared deviations) over the 16 lanes of a lane group: 16
+// consecutive columns of a row.
+__device__ inline float2 row_stats(float x) {
+  const float mean = group_sum(x) * 0.0625f, e = x - mean;
+  return make_float2(mean, group_sum(e * e));
+}
+
+// C = f(A) W^T on the fp32 matrix cores (v_mfma_f32_16x16x4f32), f = LayerNorm
+// of A's rows (LN) or nothing.  A workgroup takes a tile of 16 MB rows x 16 NB
+// columns and splits K over its NW waves: wave w takes slabs (of 32 k) [w G /
+// NW, (w + 1) G / NW) of the G = K / 32, and the waves' sums meet in LDS.
+// These products are short (K = 256 or 768, 0.07-0.4 GFLOP at 512 rows): what
+// bounds them is the round trip to the operands, the rate at which a CU takes
+// them from L2, and the launch.  So a wave asks for SB slabs of both operands
+// at once, by direct loads into LDS that only it reads (no barrier), eight
+// rows of 128 bytes per load: whole lines reach 127-140 GB/s per CU, the
+// matrix cores' own operand shape (16 rows of 64 bytes) read straight into
+// registers 37 GB/s.  Per boundary of 512 traces (d_model 256, d_ff 768, two
+// layers) the eight products take 56 us; split over workgroups, the split sums
+// through memory and a launch each to add them and take the LayerNorm, they
+// and the four reduces took 70 us.
+//
+// LDS: a slab's rows are 128 bytes; row r's 16-byte chunk c sits at position
+// c ^ ((r >> 1) & 7), so the 16 rows of an operand read fall on 16 different
+// bank groups.  A lane reads 4 consecutive k of its row (16 bytes) and feeds
+// them to 4 successive products: lane (q, i) contributes A[i][4q + kk] and
+// W[i][4q + kk] to product kk, the same k for both operands; result element
+// (4 (l / 16) + r, l % 16) sits in lane l, register r.
+//
+// LN: the rows' mean and mean squared deviation come from the kernel that
+// wrote A, as (mean, sum of squared deviations) of every 16 columns
+// (row_stats): equal counts, so the row's mean is the mean of the means and
+// its squared deviations are the blocks' plus 16 times those of their means.
+// (Measured and not kept: the row's sums taken from the operands, two barriers,
+// 12.9 against 9.5 us for SwiGLU; the products on x as it is with W scaled by
+// the gain, mean and bias added at the end, 11.6 us; eight waves of one slab
+// instead of four of two, 10.8 us.)
+//
+// Epilogues: kEpiNone C = sum; kEpiAdd C += sum (the residual; C is not read
+// by another workgroup) and the new row's statistics; kEpiSwiGLU: W holds W_1
+// and W_3 rows interleaved in groups of 16, so column blocks 2 c and 2 c + 1
+// are W_1 and W_3 of the same 16 outputs, and C[m][16 c + i] = SiLU(a1) * a3
+// with row stride N / 2.
+template <int MB, int NB, int NW, int SB, bool LN, int EPI>
+__global__ __launch_bounds__(64 * NW) void gemm_kernel(const float* A, const float* W, float* C, int M, int N, int K,
+                                                       const float* lg, const float* lb, float2* stats) {
+  static_assert(EPI != kEpiSwiGLU || NB % 2 == 0, "W_1 and W_3 blocks in pairs");
+  constexpr int kSlab = 16 * (MB + NB) * 128;  // bytes of one slab of both operands: A's rows, then W's
+  constexpr int kLoads = 2 * (MB + NB);        // 1 KB loads per slab
+  constexpr int T4 = MB * NB * 64;             // the tile in f32x4
+  constexpr int kLds = NW * SB * kSlab > NW * T4 * 16 ? NW * SB * kSlab : NW * T4 * 16;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[kLds];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lq = lane >> 4;
+  const int m0 = blockIdx.y * 16 * MB, n0 = blockIdx.x * 16 * NB;
+  const int G = K / 32, g0 = wave * G / NW, g1 = (wave + 1) * G / NW;
+  uint8_t* mine = lds + wave * SB * kSlab;
+  // load d of a slab: rows 8 d .. 8 d + 7 (A's, then W's), lane l chunk
+  // position l % 8 of row l / 8; rows past M re-read the last (never stored)
+  auto fetch = [&](int g, int slot) {
+    uint8_t* dst = mine + slot * kSlab;
+#pragma unroll
+    for (int d = 0; d < kLoads; ++d) {
+      const int r = 8 * d + (lane >> 3);
+      const int k = 32 * g + 4 * ((lane & 7) ^ ((r >> 1) & 7));
+      const float* src = d < 2 * MB ? A + (size_t)min(m0 + r, M - 1) * K + k : W + (size_t)(n0 + r - 16 * MB) * K + k;
+      dma16(src, dst + d * 1024);
+    }
+  };
+  // the rows' statistics: lane (q, i) takes blocks q nb .. q nb + nb - 1 of
+  // row i, the first four in registers
+  const int nb = K / 64;
+  const float2* sp[LN ? MB : 1];
+  float2 st[LN ? MB : 1][4];
+  if constexpr (LN) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      sp[i] = stats + (size_t)min(m0 + 16 * i + li, M - 1) * (K / 16) + lq * nb;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) st[i][k] = sp[i][min(k, nb - 1)];
+    }
+  }
+  f32x4 gv[LN ? 2 : 1], bv[LN ? 2 : 1];  // gain and bias of the slab's two halves
+  auto load_ln = [&](int g) {
+    if constexpr (LN) {
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        gv[x] = *reinterpret_cast<const f32x4*>(lg + 32 * g + 16 * x + 4 * lq);
+        bv[x] = *reinterpret_cast<const f32x4*>(lb + 32 * g + 16 * x + 4 * lq);
+      }
+    }
+  };
+  if (g0 < g1) load_ln(g0);
+#pragma unroll
+  for (int k = 0; k < SB; ++k)
+    if (g0 + k < g1) fetch(g0 + k, k);
+  float rstd[MB], shift[MB];  // LN(x) = (x rstd + shift) gain + bias
+  if constexpr (LN) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      float s = 0.f, v = 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s += k < nb ? st[i][k].x : 0.f;
+      for (int k = 4; k < nb; ++k) s += sp[i][k].x;
+      const float mean = row_sum(s) / (4 * nb);
+      auto dev = [&](const float2& x) {
+        const float e = x.x - mean;
+        return x.y + 16.f * e * e;
+      };
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v += k < nb ? dev(st[i][k]) : 0.f;
+      for (int k = 4; k < nb; ++k) v += dev(sp[i][k]);
+      rstd[i] = 1.f / sqrtf(row_sum(v) / K + kSeqLnEps);
+      shift[i] = -mean * rstd[i];
+    }
+  }
+  f32x4 acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int at = li * 128, sw = (li >> 1) & 7;
+  for (int g = g0, slot = 0; g < g1; ++g) {
+    // slab g is in: of the slabs asked for after it (at most SB - 1), each is
+    // kLoads loads
+    switch (min(SB - 1, g1 - 1 - g)) {
+      case 2: wait_vmcnt<2 * kLoads>(); break;
+      case 1: wait_vmcnt<kLoads>(); break;
+      default: wait_vmcnt<0>(); break;
+    }
+    asm volatile("" ::: "memory");
+    const uint8_t* src = mine + slot * kSlab + at;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int pos = ((4 * x + lq) ^ sw) * 16;
+      f32x4 a[MB], w[NB];
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        a[i] = *reinterpret_cast<const f32x4*>(src + i * 2048 + pos);
+        if constexpr (LN) a[i] = (a[i] * rstd[i] + shift[i]) * gv[x] + bv[x];
+      }
+#pragma unroll
+      for (int j = 0; j < NB; ++j) w[j] = *reinterpret_cast<const f32x4*>(src + (MB + j) * 2048 + pos);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], w[j][e], acc[i][j], 0, 0, 0);
+    }
+    if (g + 1 < g1) load_ln(g + 1);
+    if (g + SB < g1) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this slab's reads are done
+      fetch(g + SB, slot);
+    }
+    slot = slot + 1 == SB ? 0 : slot + 1;
+  }
+  __syncthreads();  // every wave is done with its slabs
+  f32x4* sums = reinterpret_cast<f32x4*>(lds);
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) sums[wave * T4 + (i * NB + j) * 64 + lane] = acc[i][j];
+  __syncthreads();
+  auto total = [&](int p) {  // the waves' sums, in order
+    f32x4 v = sums[p];
+#pragma unroll
+    for (int x = 1; x < NW; ++x) v += sums[x * T4 + p];
+    return v;
+  };
+  if constexpr (EPI == kEpiSwiGLU) {
+    for (int p = wave; p < MB * NB / 2; p += NW) {
+      const int i = p / (NB / 2), c = p % (NB / 2);
+      const f32x4 x = total((i * NB + 2 * c) * 64 + lane), y = total((i * NB + 2 * c + 1) * 64 + lane);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = m0 + 16 * i + 4 * lq + r;
+        if (m < M) C[(size_t)m * (N / 2) + n0 / 2 + 16 * c + li] = x[r] / (1.f + expf(-x[r])) * y[r];
+      }
+    }
+  } else {
+    for (int p = wave; p < MB * NB; p += NW) {
+      const int i = p / NB, j = p % NB;
+      f32x4 v = total(p * 64 + lane);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = m0 + 16 * i + 4 * lq + r;
+        float* o = C + (size_t)min(m, M - 1) * N + n0 + 16 * j + li;
+        if constexpr (EPI == kEpiAdd) {
+          v[r] += *o;
+          const float2 rs = row_stats(v[r]);
+          if (li == 0 && m < M) stats[(size_t)m * (N / 16) + n0 / 16 + j] = rs;
+        }
+        if (m < M) *o = v[r];
+      }
+    }
+  }
+}
+
 __device__ inline float block_sum(float v, float* red) {
   v = wave_sum(v);
   __syncthreads();  // red[] is free
@@ -188,53 +283,34 @@ __device__ inline float block_sum(float v, float* red) {
   return ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-// The LayerNorm of row x[base ..] (s: this thread's sum of the columns it
-// wrote), then u = LN(x) or the output head.
-__device__ inline void ln_tail(float s, const float* x, size_t base, int d, const float* g, const float* b, float* u,
-                               int head, const SeqDev& S, float* scores, int row, float* red) {
-  const float mean = block_sum(s, red) / d;
-  float v = 0.f;
-  for (int i = threadIdx.x; i < d; i += 256) {
-    const float e = x[base + i] - mean;
-    v += e * e;
-  }
-  const float rstd = 1.f / sqrtf(block_sum(v, red) / d + kSeqLnEps);
-  if (!head) {
-    for (int i = threadIdx.x; i < d; i += 256) u[base + i] = (x[base + i] - mean) * rstd * g[i] + b[i];
-    return;
-  }
-  float z = 0.f;
-  for (int i = threadIdx.x; i < d; i += 256)
-    z += ((x[base + i] - mean) * rstd * S.ln_out_g[i] + S.ln_out_b[i]) * S.w_out[i];
-  z = block_sum(z, red);
-  if (threadIdx.x == 0) {
+// The output head, one wave per row: LN_out of x (mean, then the mean squared
+// deviation), scores[row] = sigmoid(w_out . LN_out(x)), and the trace's step
+// count advances.
+__global__ __launch_bounds__(256) void head_kernel(const float* x, int d, SeqDev S, float* scores, int n) {
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (row >= n) return;
+  const f32x4* xr = reinterpret_cast<const f32x4*>(x + (size_t)row * d);
+  const f32x4 *g = reinterpret_cast<const f32x4*>(S.ln_out_g), *b = reinterpret_cast<const f32x4*>(S.ln_out_b),
+              *w = reinterpret_cast<const f32x4*>(S.w_out);
+  const int nd = d / 4;
+  // the lane's first element group of everything (all of d_model 256) at once
+  const int at = min(lane, nd - 1);
+  const f32x4 x0 = xr[at], g0 = g[at], b0 = b[at], w0 = w[at];
+  const bool in = lane < nd;
+  auto sum4 = [](const f32x4& v) { return (v[0] + v[1]) + (v[2] + v[3]); };
+  float s = in ? sum4(x0) : 0.f;
+  for (int i = lane + 64; i < nd; i += 64) s += sum4(xr[i]);
+  const float mean = wave_sum(s) / d;
+  float v = in ? sum4((x0 - mean) * (x0 - mean)) : 0.f;
+  for (int i = lane + 64; i < nd; i += 64) v += sum4((xr[i] - mean) * (xr[i] - mean));
+  const float rstd = 1.f / sqrtf(wave_sum(v) / d + kSeqLnEps);
+  float z = in ? sum4(((x0 - mean) * rstd * g0 + b0) * w0) : 0.f;
+  for (int i = lane + 64; i < nd; i += 64) z += sum4(((xr[i] - mean) * rstd * g[i] + b[i]) * w[i]);
+  z = wave_sum(z);
+  if (lane == 0) {
     scores[row] = 1.f / (1.f + expf(-z));
     S.lens[S.ids[row]] += 1;
   }
-}
-
-__global__ __launch_bounds__(256) void reduce_ln_kernel(const float* part, int splits, const float* R,
-                                                        float* x, int d, const float* g, const float* b, float* u,
-                                                        int head, SeqDev S, float* scores, int n) {
-  __shared__ float red[4];
-  const int row = blockIdx.x;
-  const size_t MN = (size_t)n * d, base = (size_t)row * d;
-  float s = 0.f;
-  for (int i = threadIdx.x; i < d; i += 256) {
-    float y = 0.f;
-    for (int z0 = 0; z0 < splits; z0 += 8) {
-      float v[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = part[(size_t)min(z0 + e, splits - 1) * MN + base + i];
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (z0 + e < splits) y += v[e];
-    }
-    y += R[base + i];
-    x[base + i] = y;
-    s += y;
-  }
-  ln_tail(s, x, base, d, g, b, u, head, S, scores, row, red);
 }
 
 // The input projection's reduce, one workgroup per row: the input
@@ -242,16 +318,14 @@ __global__ __launch_bounds__(256) void reduce_ln_kernel(const float* part, int s
 // the split partial sums of h W'^T over the three planes (parts
 // [splits][n][3 d]: plane p of column i at p d + i), added split by split in
 // order, then x = GELU(rstd (y - mean c[i]) + dv[i]) (LN_in(h) W_in^T
-// rearranged: c = the row sums of W', dv = W_in b), then ln_tail.  The
-// state's first 4096 values (four 8-byte loads per thread, kept in
+// rearranged: c = the row sums of W', dv = W_in b).  The state's first 4096 values (four 8-byte loads per thread, kept in
 // registers for both statistics passes) and the first column's partial sums
 // of up to kInBatch splits are all requested before any of them is used.
 constexpr int kInBatch = 12;
 
 __global__ __launch_bounds__(256) void reduce_in_kernel(const uint16_t* h, int dim, const float* part, int splits,
-                                                        const float* c, const float* dv, float* x, int d,
-                                                        const float* g, const float* b, float* u, int head, SeqDev S,
-                                                        float* scores, int n) {
+                                                        const float* c, const float* dv, float* x, int d, float2* stats,
+                                                        int n) {
   __shared__ float red[4];
   const int row = blockIdx.x, tid = threadIdx.x;
   const uint2* h4 = reinterpret_cast<const uint2*>(h + (size_t)row * dim);  // four bf16 per load
@@ -304,7 +378,6 @@ __global__ __launch_bounds__(256) void reduce_in_kernel(const uint16_t* h, int d
     for (int k = 0; k < 4; ++k) hv += (e[k] - hmean) * (e[k] - hmean);
   }
   const float hrstd = 1.f / sqrtf(block_sum(hv, red) / dim + kSeqLnEps);
-  float s = 0.f;
   for (int i = tid; i < d; i += 256) {
     float y = 0.f;
     for (int z0 = 0; z0 < splits; z0 += kInBatch) {
@@ -315,9 +388,9 @@ __global__ __launch_bounds__(256) void reduce_in_kernel(const uint16_t* h, int d
     }
     y = gelu_erf(hrstd * (y - hmean * c[i]) + dv[i]);
     x[base + i] = y;
-    s += y;
+    const float2 st = row_stats(y);  // d is a multiple of 16: whole lane groups
+    if ((tid & 15) == 0) stats[base / 16 + i / 16] = st;
   }
-  ln_tail(s, x, base, d, g, b, u, head, S, scores, row, red);
 }
 
 // The input projection's weights for the bf16 matrix cores, one workgroup
@@ -535,17 +608,44 @@ __global__ void seq_set_len_kernel(SeqDev S, const int32_t* ids, int n, int valu
 
 }  // namespace
 
-hipError_t seq_gemm(const float* A, const float* W, float* C, int M, int N, int K, int splits, int epi, float* part,
-                    hipStream_t s) {
-  const int ks = K / splits;
-  // 64-row tiles when they alone give the GPU ~256 workgroups, else 32-row
-  const bool wide = (long)(N / 64) * ((M + 63) / 64) * splits >= 256;
-  const dim3 grid(N / 64, wide ? (M + 63) / 64 : (M + 31) / 32, splits);
-  if (wide)
-    hipLaunchKernelGGL((gemm_kernel<64>), grid, dim3(256), 0, s, A, W, C, M, N, K, ks, epi, part);
-  else
-    hipLaunchKernelGGL((gemm_kernel<32>), grid, dim3(256), 0, s, A, W, C, M, N, K, ks, epi, part);
+// Tiles: a product of few rows takes the smallest ones (more workgroups, and
+// none of them long); where larger ones still give the chip ~200 workgroups,
+// each operand is read by fewer of them.  At 512 rows, d_model 256, d_ff 768:
+// QKV 32 x 48 (6.9 us), SwiGLU 32 x 96 (9.5 us), the d_model-wide ones 16 x 32
+// (W_o 4.9, W_2 6.7 us), 256 workgroups each; 24 rows of d_model 128: 3.6-4.7
+// us each.
+template <int MB, int NB, int NW, int KG, bool LN, int EPI>
+static hipError_t launch_gemm(const float* A, const float* W, float* C, int M, int N, int K, const float* lg,
+                              const float* lb, float2* stats, hipStream_t s) {
+  hipLaunchKernelGGL((gemm_kernel<MB, NB, NW, KG, LN, EPI>), dim3(N / (16 * NB), (M + 16 * MB - 1) / (16 * MB)),
+                     dim3(64 * NW), 0, s, A, W, C, M, N, K, lg, lb, stats);
   return hipGetLastError();
+}
+// Workgroups of tiles of `rows` x `cols`.
+static long tiles(int M, int N, int rows, int cols) { return (long)((M + rows - 1) / rows) * (N / cols); }
+
+hipError_t seq_gemm_ln(const float* A, const float* W, float* C, int M, int N, int K, const float* lg, const float* lb,
+                       const float2* stats, hipStream_t s) {
+  float2* st = const_cast<float2*>(stats);
+  if (tiles(M, N, 32, 48) >= 192) return launch_gemm<2, 3, 4, 2, true, kEpiNone>(A, W, C, M, N, K, lg, lb, st, s);
+  return launch_gemm<1, 1, 8, 1, true, kEpiNone>(A, W, C, M, N, K, lg, lb, st, s);
+}
+
+hipError_t seq_gemm_ln_swiglu(const float* A, const float* W, float* C, int M, int N, int K, const float* lg,
+                              const float* lb, const float2* stats, hipStream_t s) {
+  float2* st = const_cast<float2*>(stats);
+  if (N % 96 == 0 && tiles(M, N, 32, 96) >= 192)
+    return launch_gemm<2, 6, 4, 2, true, kEpiSwiGLU>(A, W, C, M, N, K, lg, lb, st, s);
+  if (tiles(M, N, 32, 64) >= 192) return launch_gemm<2, 4, 8, 1, true, kEpiSwiGLU>(A, W, C, M, N, K, lg, lb, st, s);
+  return launch_gemm<1, 2, 8, 1, true, kEpiSwiGLU>(A, W, C, M, N, K, lg, lb, st, s);
+}
+
+hipError_t seq_gemm_add(const float* A, const float* W, float* C, int M, int N, int K, float2* stats, hipStream_t s) {
+  if (tiles(M, N, 16, 32) >= 192) {
+    if (K > 256) return launch_gemm<1, 2, 8, 3, false, kEpiAdd>(A, W, C, M, N, K, nullptr, nullptr, stats, s);
+    return launch_gemm<1, 2, 4, 2, false, kEpiAdd>(A, W, C, M, N, K, nullptr, nullptr, stats, s);
+  }
+  return launch_gemm<1, 1, 8, 2, false, kEpiAdd>(A, W, C, M, N, K, nullptr, nullptr, stats, s);
 }
 
 hipError_t seq_prep_input(const float* w_in, const float* ln_g, const float* ln_b, int dim, int dm, uint16_t* planes,
@@ -555,17 +655,13 @@ hipError_t seq_prep_input(const float* w_in, const float* ln_g, const float* ln_
 }
 
 hipError_t seq_reduce_in(const uint16_t* h, int dim, const float* part, int splits, const float* c, const float* dv,
-                         float* x, int d, const float* g, const float* b, float* u, bool head, const SeqDev& S,
-                         float* scores, int n, hipStream_t s) {
-  hipLaunchKernelGGL(reduce_in_kernel, dim3(n), dim3(256), 0, s, h, dim, part, splits, c, dv, x, d, g, b, u,
-                     (int)head, S, scores, n);
+                         float* x, int d, float2* stats, int n, hipStream_t s) {
+  hipLaunchKernelGGL(reduce_in_kernel, dim3(n), dim3(256), 0, s, h, dim, part, splits, c, dv, x, d, stats, n);
   return hipGetLastError();
 }
 
-hipError_t seq_reduce_ln(const float* part, int splits, const float* R, float* x, int d, const float* g,
-                         const float* b, float* u, bool head, const SeqDev& S, float* scores, int n, hipStream_t s) {
-  hipLaunchKernelGGL(reduce_ln_kernel, dim3(n), dim3(256), 0, s, part, splits, R, x, d, g, b, u, (int)head, S,
-                     scores, n);
+hipError_t seq_head(const float* x, int d, const SeqDev& S, float* scores, int n, hipStream_t s) {
+  hipLaunchKernelGGL(head_kernel, dim3((n + 3) / 4), dim3(256), 0, s, x, d, S, scores, n);
   return hipGetLastError();
 }
 

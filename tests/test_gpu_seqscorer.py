@@ -233,3 +233,26 @@ def test_histories_past_one_pass_of_the_attention_step():
                 assert abs(got[i] - want) <= TOL, (r, t, got[i], want)
     assert [gpu.steps(t) for t in range(cfg.slots)] == [289, 289, 289, 289]  # the fork copied 140 steps
     gpu.check()
+
+
+@pytest.mark.parametrize("n,heads,d_ff", [
+    (33, 1, 64),     # small tiles, fewer k slabs than waves, a partial last row tile
+    (40, 17, 192),   # d_model 1088: more slabs than a wave holds, rows wider than one pass of the head
+    (300, 4, 704),   # SwiGLU in 32 x 64 tiles (2 d_ff not a multiple of 96)
+    (401, 4, 768),   # every wide tile, a partial last row tile
+    (401, 3, 320),   # d_model 192: an uneven split of K over the waves
+])
+def test_product_tiles(n, heads, d_ff):
+    """The products' tile variants and K splits: two boundaries, rows at the
+    tiles' edges against the oracle."""
+    import dataclasses
+    cfg = dataclasses.replace(SEQ_SMALL, d_model=64 * heads, n_heads=heads, n_layers=1, d_ff=d_ff, max_steps=3, slots=n)
+    w, gpu, _ = _make(cfg)
+    H = [step_states(cfg, r)[:n] for r in range(2)]
+    got = [gpu.step(list(range(n)), _bf16(h)).cpu().numpy() for h in H]
+    for t in sorted({0, 1, 15, 16, 31, 32, n // 2, n - 17, n - 2, n - 1} & set(range(n))):
+        hist = np.stack([bf16_to_f64(h[t]) for h in H])
+        for r in range(2):
+            want = scorer_outputs(w, hist[:r + 1], heads)[-1]
+            assert abs(got[r][t] - want) <= TOL, (t, r, got[r][t], want)
+    gpu.check()

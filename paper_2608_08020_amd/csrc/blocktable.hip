@@ -138,49 +138,83 @@ __global__ __launch_bounds__(kAllocThreads) void alloc_kernel(DevPool P, const i
   }
 }
 
-// Copy one token's K and V (all KV heads) into its cache slot: K in 16-byte
-// d-chunks at token row k_phys(row), V element-wise into the transposed tile.
-__device__ inline void copy_token(const DevPool& P, int blk, int row, const uint8_t* ksrc,
-                                  const uint8_t* vsrc) {
-  const int es = P.esize;
-  const int row_bytes = kHeadDim * es;  // one head, one token
-  const int kchunks = row_bytes / 16;
-  const size_t tile = (size_t)kBlock * row_bytes;
-  const size_t blk0 = (size_t)blk * P.Hkv * tile;
-  const int pr = k_phys(row);
-  for (int c = threadIdx.x; c < P.Hkv * kchunks; c += blockDim.x) {
-    const int head = c / kchunks, cc = c % kchunks;
-    const size_t dst = blk0 + head * tile + ((size_t)cc * kBlock + pr) * 16;
-    *reinterpret_cast<uint4*>(P.k_cache + dst) = *reinterpret_cast<const uint4*>(ksrc + (size_t)c * 16);
-  }
-  for (int e = threadIdx.x; e < P.Hkv * kHeadDim; e += blockDim.x) {
-    const int head = e / kHeadDim, d = e % kHeadDim;
-    const size_t dst = blk0 + head * tile + ((size_t)d * kBlock + row) * es;
-    if (es == 2)
-      *reinterpret_cast<uint16_t*>(P.v_cache + dst) = reinterpret_cast<const uint16_t*>(vsrc)[e];
-    else
-      P.v_cache[dst] = vsrc[e];
-  }
+// 16 bytes of the caller's K or V (no alignment beyond the element's is asked
+// of those buffers).
+struct __attribute__((packed, aligned(1))) Raw16 {
+  uint32_t w[4];
+};
+__device__ inline uint4 ld_raw16(const uint8_t* p) {
+  const Raw16 r = *reinterpret_cast<const Raw16*>(p);
+  return make_uint4(r.w[0], r.w[1], r.w[2], r.w[3]);
 }
 
-// One workgroup per (token, layer); k, v: [layers][n][Hkv][128], started
-// scales: [layers][started][2].
-__global__ void write_kernel(DevPool P0, int32_t trace, int32_t pos0, int32_t n, const uint8_t* k,
-                             const uint8_t* v, const float* started_scales, int32_t started) {
-  const int i = blockIdx.x, l = blockIdx.y;
+// A run of tokens into one layer's caches: one workgroup per (block, KV head,
+// layer), one thread per 16-byte chunk of a tile (ES = bytes per element, 128
+// ES threads).  Bound by HBM.  Both tiles are read in whole token rows (256
+// or 128 bytes) and turned in LDS, so that every store is 16 bytes of a tile
+// written in order: K into its d-chunks at token row k_phys(row), V into
+// [d][token].  V's rows are padded by 8 bytes in LDS: the two token halves
+// that a wave gathers fall in different banks; K's chunks by 16.  A block that
+// the run covers in part keeps its other tokens: K's chunks are whole tokens,
+// a V chunk that is not whole is stored by element.
+//   k, v: [layers][n][Hkv][128]; started scales: [layers][started][2]
+template <int ES>
+__global__ __launch_bounds__(128 * ES) void write_kernel(DevPool P0, int32_t trace, int32_t pos0, int32_t n,
+                                                         const uint8_t* k, const uint8_t* v,
+                                                         const float* started_scales, int32_t started) {
+  constexpr int kRow = kHeadDim * ES, kChunks = kRow / 16, kPer = 16 / ES;  // bytes and chunks a token, elements a chunk
+  constexpr int kVRow = kRow + 8, kKCol = kBlock * 16 + 16;
+  __shared__ __attribute__((aligned(16))) uint8_t klds[kChunks * kKCol], vlds[kBlock * kVRow];
+  const int head = blockIdx.x % P0.Hkv, l = blockIdx.y, t = threadIdx.x;
+  const int j = pos0 / kBlock + (int)(blockIdx.x / P0.Hkv);  // logical block
   const DevPool P = P0.layer(l);
-  const int pos = pos0 + i;
-  const int blk = P.table[(size_t)trace * P.max_blocks + pos / kBlock];
-  if ((unsigned)blk >= (unsigned)P.num_blocks) {
-    if (threadIdx.x == 0) atomicOr(P.err, kErrBadBlock);
+  const int r0 = max(pos0 - j * kBlock, 0), r1 = min(pos0 + n - j * kBlock, kBlock);  // its rows in the run
+  const int blk = P.table[(size_t)trace * P.max_blocks + j];
+  {
+    const int row = t / kChunks, c = t % kChunks;
+    // rows outside the run re-read one inside it (never stored)
+    const int tok = j * kBlock + min(max(row, r0), r1 - 1) - pos0;
+    const size_t src = (((size_t)l * n + tok) * P.Hkv + head) * kRow + c * 16;
+    const uint4 kk = ld_raw16(k + src), vv = ld_raw16(v + src);
+    *reinterpret_cast<uint4*>(klds + c * kKCol + k_phys(row) * 16) = kk;
+    uint2* vd = reinterpret_cast<uint2*>(vlds + row * kVRow + c * 16);
+    vd[0] = make_uint2(vv.x, vv.y);
+    vd[1] = make_uint2(vv.z, vv.w);
+  }
+  if ((unsigned)blk >= (unsigned)P.num_blocks) {  // uniform over the workgroup
+    if (t == 0) atomicOr(P.err, kErrBadBlock);
     return;
   }
-  const size_t tok_bytes = (size_t)P.Hkv * kHeadDim * P.esize;
-  const size_t src = ((size_t)l * n + i) * tok_bytes;
-  copy_token(P, blk, pos % kBlock, k + src, v + src);
-  if (started_scales && threadIdx.x == 0 && pos % kBlock == 0) {
-    const int first = (pos0 + kBlock - 1) / kBlock * kBlock;
-    const int k2 = l * started + (pos - first) / kBlock;
+  __syncthreads();
+  const size_t tile = ((size_t)blk * P.Hkv + head) * kBlock * kRow;
+  const int krow = k_phys(t % kBlock);  // k_phys is its own inverse
+  if (krow >= r0 && krow < r1)
+    *reinterpret_cast<uint4*>(P.k_cache + tile + t * 16) =
+        *reinterpret_cast<const uint4*>(klds + (t / kBlock) * kKCol + (t % kBlock) * 16);
+  const int d = t / ES, f = (t % ES) * kPer;  // the chunk's tokens: f .. f + kPer - 1 of element d
+  uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const uint8_t* src = vlds + (f + e) * kVRow + d * ES;
+    const uint32_t x = ES == 2 ? *reinterpret_cast<const uint16_t*>(src) : *src;
+    w[e * ES / 4] |= x << (8 * (e * ES % 4));
+  }
+  uint8_t* dst = P.v_cache + tile + t * 16;
+  if (f >= r0 && f + kPer <= r1) {
+    *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      if (f + e < r0 || f + e >= r1) continue;
+      const uint32_t x = w[e * ES / 4] >> (8 * (e * ES % 4));
+      if (ES == 2)
+        reinterpret_cast<uint16_t*>(dst)[e] = (uint16_t)x;
+      else
+        dst[e] = (uint8_t)x;
+    }
+  }
+  if (started_scales && t == 0 && head == 0 && r0 == 0) {
+    const int k2 = l * started + j - (pos0 + kBlock - 1) / kBlock;
     P.kv_scale[2 * blk] = started_scales[2 * k2];
     P.kv_scale[2 * blk + 1] = started_scales[2 * k2 + 1];
   }
@@ -297,9 +331,13 @@ hipError_t launch_write(const DevPool& P, int32_t trace, int32_t pos0, int32_t n
                         const void* v, const float* started_scales, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int first = (pos0 + kBlock - 1) / kBlock, last = (pos0 + n - 1) / kBlock;
-  hipLaunchKernelGGL(write_kernel, dim3(n, P.num_layers), dim3(128), 0, s, P, trace, pos0, n,
-                     static_cast<const uint8_t*>(k), static_cast<const uint8_t*>(v), started_scales,
-                     last >= first ? last - first + 1 : 0);
+  const int started = last >= first ? last - first + 1 : 0;
+  const dim3 grid((unsigned)(last - pos0 / kBlock + 1) * P.Hkv, P.num_layers);
+  const auto *ks = static_cast<const uint8_t*>(k), *vs = static_cast<const uint8_t*>(v);
+  if (P.esize == 2)
+    hipLaunchKernelGGL(write_kernel<2>, grid, dim3(256), 0, s, P, trace, pos0, n, ks, vs, started_scales, started);
+  else
+    hipLaunchKernelGGL(write_kernel<1>, grid, dim3(128), 0, s, P, trace, pos0, n, ks, vs, started_scales, started);
   return hipGetLastError();
 }
 

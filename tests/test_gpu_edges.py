@@ -301,3 +301,41 @@ def test_launch_argument_capacity_boundary(opening):
         ref = decode_attention(bf16_to_f64(q[i]), K, V, 1 / math.sqrt(128))
         assert_attn_close(out[i], ref, f"trace {ids[i]} (list position {i})")
     p.pool_check()
+
+
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("hkv,layers", [(1, 1), (2, 3), (8, 2)])
+def test_write_places_every_element_and_nothing_else(kv_dtype, hkv, layers):
+    """Runs that start and end inside blocks, K and V at any element address:
+    every element at its place in the tiles, every other byte as it was."""
+    fp8 = kv_dtype == "fp8_e4m3"
+    nb, es = 12, 1 if fp8 else 2
+    p = Pool(num_blocks=nb, num_q_heads=4 * hkv, num_kv_heads=hkv, max_traces=2, max_blocks_per_trace=8,
+             kv_dtype=kv_dtype, num_layers=layers)
+    p.kv_alloc([1], [7])      # the run's blocks are not the pool's first
+    p.kv_alloc([0], [128])
+    for c in (p.k_cache, p.v_cache):
+        c.view(torch.uint8).fill_(0xA5)
+    blocks = p.block_table.cpu().numpy()[0]
+    want = np.full((2, layers, nb, hkv, 16 * 128 * es), 0xA5, np.uint8)
+    # tile offsets of element d of token row r: K [d / C][row with bits 2 and 3 swapped][d % C], V [d][r]
+    C = 16 // es
+    r, d = np.meshgrid(np.arange(16), np.arange(128), indexing="ij")
+    phys = (r & 3) | ((r >> 1) & 4) | ((r << 1) & 8)
+    place = [(d // C * 16 + phys) * C + d % C, d * 16 + r]
+    rng = np.random.default_rng(hkv)
+    for pos0, n, off in [(0, 1, 0), (0, 16, 1), (5, 7, 3), (13, 20, 0), (31, 1, 1), (32, 1, 0), (40, 56, 5), (97, 31, 0)]:
+        raw = rng.integers(0, 256, (2, off + layers * n * hkv * 128, es), np.uint8)
+        dev = torch.from_numpy(raw).to(DEV).view(torch.uint8 if fp8 else torch.bfloat16).view(2, -1)
+        k, v = (x[off:].view(layers, n, hkv, 128) for x in dev)
+        m = -(-(pos0 + n) // 16) - -(-pos0 // 16)
+        p.kv_write(0, pos0, k, v, np.ones((layers, m, 2), np.float32) if fp8 and m else None)
+        src = raw[:, off:].reshape(2, layers, n, hkv, 128, es)
+        for w in (0, 1):
+            tiles = want[w].reshape(layers, nb, hkv, 2048, es)
+            for i in range(n):
+                tiles[:, blocks[(pos0 + i) // 16]][:, :, place[w][(pos0 + i) % 16]] = src[w, :, i]
+    got = [c.view(torch.uint8).cpu().numpy().reshape(want[0].shape) for c in (p.k_cache, p.v_cache)]
+    for w in (0, 1):
+        assert np.array_equal(got[w], want[w]), "KV"[w]
+    p.pool_check()

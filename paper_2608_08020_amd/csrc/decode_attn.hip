@@ -274,14 +274,22 @@ __device__ inline int query_row(const AttnLaunch& A, const AttnUnit& U, int Hq, 
   return r < R ? pos * Hq + h : -1;
 }
 
-// Partials: lane (q, lr) holds O[row lr][16 r + 4 q + e] in acc[r][e].
+// Partials: lane (q, lr) holds O[row lr][16 r + 4 q + e] in acc[r][e].  They
+// are read once, by the merge: a set that fits the L2s stays there for it, a
+// larger one (STREAM) would only push out what is still to be read.
+template <bool STREAM>
 __device__ inline void write_partial(const AttnLaunch& A, const AttnUnit& U, int qrow, int q, const RowState& st) {
   const float l = wave_sum_over_groups(st.l);
   if (qrow < 0) return;
   const size_t idx = (size_t)qrow * A.kmax + U.kidx;
   f32x4* dst = reinterpret_cast<f32x4*>(A.part_acc + idx * kHeadDim + 4 * q);
 #pragma unroll
-  for (int k = 0; k < 8; ++k) __builtin_nontemporal_store(st.acc[k], dst + 4 * k);  // read once, by the merge
+  for (int k = 0; k < 8; ++k) {
+    if constexpr (STREAM)
+      __builtin_nontemporal_store(st.acc[k], dst + 4 * k);
+    else
+      dst[4 * k] = st.acc[k];
+  }
   if (q == 0) A.part_ml[idx] = float2{st.m, l};
 }
 
@@ -649,7 +657,7 @@ __device__ inline int append_token(const DevPool& P, const AttnLaunch& A, const 
 // softmax and P.V of tile i, so the matrix cores and the vector ALUs
 // overlap; a buffer's K half is refilled with tile j + 2 right after QK(j)
 // and its V half right after P.V(j), so two tiles are always in flight.
-template <bool FP8, int RB>
+template <bool FP8, int RB, bool STREAM>
 __device__ void narrow_unit(const DevPool& P, const AttnLaunch& A, const AttnUnit& U, int lane, uint8_t* qlds) {
   const int32_t* brow = P.table + (size_t)U.owner * P.max_blocks + U.jb0;
   const bool open = U.nblk < 0;  // the run ends where its trace does, the new token included
@@ -763,7 +771,7 @@ __device__ void narrow_unit(const DevPool& P, const AttnLaunch& A, const AttnUni
     if (i + 1 < ntile) step(i + 1, tb, mb, nb, ta, na);
   }
 #pragma unroll
-  for (int r = 0; r < RB; ++r) write_partial(A, U, qrow[r], g.q, st[r]);
+  for (int r = 0; r < RB; ++r) write_partial<STREAM>(A, U, qrow[r], g.q, st[r]);
 }
 
 // ----------------------------------------------------------- cooperative --
@@ -831,7 +839,7 @@ __device__ inline void wait_tiles_per(int later) {
 // stages hold the raw tiles in the cache's layout, and every wave widens
 // the operands it reads (as the narrow path does from HBM), so an fp8 tile
 // moves half the bytes and the ring is deeper.
-template <bool FP8, int RB>
+template <bool FP8, int RB, bool STREAM>
 __device__ void coop_unit(const DevPool& P, const AttnLaunch& A, const AttnUnit& U, int wave, int lane,
                           uint8_t* lds) {
   constexpr int ring = FP8 ? kRing8 : kRing, ahead = FP8 ? kAhead8 : kAhead;
@@ -1013,7 +1021,7 @@ __device__ void coop_unit(const DevPool& P, const AttnLaunch& A, const AttnUnit&
   }
   if (active) {
 #pragma unroll
-    for (int r = 0; r < RB; ++r) write_partial(A, U, qrow[r], g.q, st[r]);
+    for (int r = 0; r < RB; ++r) write_partial<STREAM>(A, U, qrow[r], g.q, st[r]);
   }
 }
 
@@ -1034,7 +1042,7 @@ __device__ inline int xcd_slots(const AttnLaunch& A, int x) {
   return (A.xcd_off[x + 1] - A.xcd_off[x]) / kUnitsPerWG;
 }
 
-template <bool FP8>
+template <bool FP8, bool STREAM>
 __global__ __launch_bounds__(kThreads, 2) void attn_units_kernel(DevPool P, AttnLaunch A) {
   __shared__ __attribute__((aligned(16))) uint8_t lds[(FP8 ? kRing8 * kStage8 : kRing * kStage) + kIdsBytes];
   static_assert(!FP8 || 4 * 8192 <= kRing8 * kStage8, "narrow waves' Q regions (two row blocks)");
@@ -1064,20 +1072,20 @@ __global__ __launch_bounds__(kThreads, 2) void attn_units_kernel(DevPool P, Attn
   if (U.flags & kUnitCoop) {
     // up to 64 rows: one row block per wave; more: two
     if ((U.mem_cnt << A.gshift) > 4 * kRowsPerUnit)
-      coop_unit<FP8, 2>(P, A, U, wave, lane, lds);
+      coop_unit<FP8, 2, STREAM>(P, A, U, wave, lane, lds);
     else if (U.mem_cnt > 0)
-      coop_unit<FP8, 1>(P, A, U, wave, lane, lds);
+      coop_unit<FP8, 1, STREAM>(P, A, U, wave, lane, lds);
     return;
   }
   // no barrier on the narrow path; fp8 units of 17-32 rows take two row
   // blocks in one wave
   if constexpr (FP8) {
     if ((U.mem_cnt << A.gshift) > kRowsPerUnit)
-      narrow_unit<FP8, 2>(P, A, U, lane, lds + wave * 8192);
+      narrow_unit<FP8, 2, STREAM>(P, A, U, lane, lds + wave * 8192);
     else if (U.mem_cnt > 0)
-      narrow_unit<FP8, 1>(P, A, U, lane, nullptr);
+      narrow_unit<FP8, 1, STREAM>(P, A, U, lane, nullptr);
   } else if (U.mem_cnt > 0) {
-    narrow_unit<FP8, 1>(P, A, U, lane, nullptr);
+    narrow_unit<FP8, 1, STREAM>(P, A, U, lane, nullptr);
   }
 }
 
@@ -1150,10 +1158,9 @@ __global__ __launch_bounds__(256) void merge_kernel(DevPool P, AttnLaunch A) {
 
 hipError_t launch_attention_units(const DevPool& P, const AttnLaunch& A, hipStream_t s) {
   if (A.n <= 0 || A.grid <= 0) return hipSuccess;
-  if (P.esize == 1)
-    hipLaunchKernelGGL(attn_units_kernel<true>, dim3(A.grid), dim3(kThreads), 0, s, P, A);
-  else
-    hipLaunchKernelGGL(attn_units_kernel<false>, dim3(A.grid), dim3(kThreads), 0, s, P, A);
+  const auto kernel = P.esize == 1 ? (A.part_stream ? attn_units_kernel<true, true> : attn_units_kernel<true, false>)
+                                   : (A.part_stream ? attn_units_kernel<false, true> : attn_units_kernel<false, false>);
+  hipLaunchKernelGGL(kernel, dim3(A.grid), dim3(kThreads), 0, s, P, A);
   return hipGetLastError();
 }
 

@@ -148,6 +148,7 @@ struct gambit_pool {
   std::vector<int32_t> plan_list;
   int xcd_off[9] = {0};
   int plan_steps = 0;              // decode steps taken with the plan
+  size_t plan_partials = 0;        // partials of one head that a launch with the plan writes
   int grid = 0;
   int n_units = 0;
   bool queues_dirty = false;       // an attention launch was not followed by its merge
@@ -732,6 +733,7 @@ gambit_status build_plan(gambit_pool* p, int n, const int32_t* ids, hipStream_t 
             "plan upload");
   HIP_TRY(p, hipEventRecord(p->plan_ev, s), "plan fence");
   p->plan_list.assign(ids, ids + n);
+  p->plan_partials = std::accumulate(nk.begin(), nk.begin() + n, (size_t)0);
   p->plan_valid = true;
   p->plan_steps = 0;
   p->stats.n_units = p->n_units;
@@ -1060,6 +1062,12 @@ static gambit_status decode_layer(gambit_pool* p, int32_t layer, int32_t n, cons
     A.part_acc = ws_ptr<float>(p, p->L.part_acc);
     A.part_ml = ws_ptr<float2>(p, p->L.part_ml);
     A.kmax = p->L.kmax;
+    // Partials that fit the eight 4 MB L2s are stored plainly, more of them
+    // with the non-temporal hint.  Per pass, with the hint -> plain: about 20
+    // MB (six fp8 layers of 45 traces) 1603 -> 1502 us, (64 traces) 1520 ->
+    // 1487 us, (256 private traces) unchanged; 59-71 MB (512 traces) 14664 ->
+    // 14845 us, (256 fp8) 3602 -> 3645 us.
+    A.part_stream = p->plan_partials * p->d.num_q_heads * gambit::kHeadDim * 4 > ((size_t)32 << 20);
     A.gshift = __builtin_ctz(p->g);
     A.resident = attn_resident(p);
     A.n = n;

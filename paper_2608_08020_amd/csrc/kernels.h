@@ -114,6 +114,7 @@ struct AttnLaunch {
   const int32_t* nk;        // [n] partials per list position
   float* part_acc;          // [n][Hq][kmax][128]
   float2* part_ml;          // [n][Hq][kmax] (running max in log2 units, sum)
+  int32_t part_stream;      // the partials leave with the non-temporal hint
   int32_t kmax;
   int32_t gshift;           // log2 of the GQA group
   int32_t resident;         // workgroup slots an XCD runs at once

@@ -1100,20 +1100,35 @@ __global__ __launch_bounds__(kThreads, 2) void attn_units_kernel(DevPool P, Attn
 // large ones (0.1 GB at 512 traces).
 constexpr int kMergeDepth = 8;
 
-__global__ __launch_bounds__(256) void merge_kernel(DevPool P, AttnLaunch A) {
+// The merge's part of a launch.  The attention launch's own arguments, with
+// their lists of new blocks, are 2.4 KB, which a launch has to write and the
+// card to fetch: given those, 64 traces took 1484 us a pass of 32 steps, with
+// these 1459; six layers of 45 traces (48 merges) 1499 and 1474 us.
+struct MergeLaunch {
+  int32_t* queues;
+  const int32_t *list, *nk;
+  const float* part_acc;
+  const float2* part_ml;
+  int32_t *seq_len, *gen;
+  void* out;
+  int32_t out_f32, kmax, n, Hq;
+  int32_t advance;  // the step's last layer: advance the lengths and GenLen
+};
+
+__global__ __launch_bounds__(256) void merge_kernel(MergeLaunch A) {
   if (blockIdx.x == 0 && threadIdx.x < 8) A.queues[threadIdx.x] = 0;  // for the next attention launch
-  if (A.len_bias && A.advance) {  // the step's token is in: advance the lengths (and GenLen, Alg. 1)
+  if (A.advance) {  // the step's token is in: advance the lengths (and GenLen, Alg. 1)
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < A.n) {
       const int t = A.list[i];
-      P.seq_len[t] += 1;
-      P.gen[t] += 1;
+      A.seq_len[t] += 1;
+      A.gen[t] += 1;
     }
   }
   const int row = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (row >= A.n * P.Hq) return;
+  if (row >= A.n * A.Hq) return;
   const int lane = threadIdx.x & 63, half = lane >> 5;
-  const int pos = row / P.Hq;
+  const int pos = row / A.Hq;
   const int nk = A.nk[pos];  // 1 <= nk <= kmax <= 64
   const float2* ml = A.part_ml + (size_t)row * A.kmax;
   const float* pa = A.part_acc + (size_t)row * A.kmax * kHeadDim + 4 * (lane & 31);
@@ -1167,7 +1182,9 @@ hipError_t launch_attention_units(const DevPool& P, const AttnLaunch& A, hipStre
 hipError_t launch_attention_merge(const DevPool& P, const AttnLaunch& A, hipStream_t s) {
   if (A.n <= 0) return hipSuccess;
   const int rows = A.n * P.Hq;
-  hipLaunchKernelGGL(merge_kernel, dim3((rows + 3) / 4), dim3(256), 0, s, P, A);
+  const MergeLaunch M{A.queues,  A.list,    A.nk, A.part_acc, A.part_ml, P.seq_len, P.gen,
+                      A.out, A.out_f32, A.kmax, A.n, P.Hq, A.len_bias && A.advance};
+  hipLaunchKernelGGL(merge_kernel, dim3((rows + 3) / 4), dim3(256), 0, s, M);
   return hipGetLastError();
 }
 

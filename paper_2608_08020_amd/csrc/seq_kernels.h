@@ -53,23 +53,21 @@ hipError_t seq_gemm_add(const float* A, const float* W, float* C, int M, int N, 
 // and dv = W_in b (one launch, at creation).
 hipError_t seq_prep_input(const float* w_in, const float* ln_g, const float* ln_b, int dim, int dm, uint16_t* planes,
                           float* c, float* dv, hipStream_t s);
-// x = GELU(LN_in(h) W_in^T) from the split partial sums of h against the
-// planes (part [splits][n][3 d]).
+// The input projection's K splits: enough 64 x 64 tiles for ~256 workgroups,
+// at most one per 64 k.
+inline int seq_in_splits(int n, int dim, int dm) {
+  const long tiles = (long)((n + 63) / 64) * (dm / 64);
+  const long s = 256 / tiles;
+  return (int)(s < 1 ? 1 : (s < dim / 64 ? s : dim / 64));
+}
+// part[s][m][c] = split s's share of h W'^T (dim a multiple of 64, dm of 64).
+hipError_t seq_proj_in(const uint16_t* h, const uint16_t* planes, int n, int dim, int dm, int splits, float* part,
+                       hipStream_t s);
+// x = GELU(LN_in(h) W_in^T) from those.
 hipError_t seq_reduce_in(const uint16_t* h, int dim, const float* part, int splits, const float* c, const float* dv,
                          float* x, int d, float2* stats, int n, hipStream_t s);
 // The output head's scores from x, and the step counts' advance.
 hipError_t seq_head(const float* x, int d, const SeqDev& S, float* scores, int n, hipStream_t s);
-// parts[s][t][u] = the sum over split s's k range of h[t][k] w[u][k], bf16
-// operands and fp32 sums, for s < splits: the MLP scorer's split-k GEMM
-// without its epilogue (mlp_scorer.hip).  dim a multiple of 128, units a
-// multiple of 4, 1 <= splits <= dim / 128; bf16_partial_splits gives the
-// MLP scorer's count (at most kMlpSplitBytes of sums when above one).
-inline int bf16_partial_splits(int32_t n, int32_t dim, int32_t units) {
-  const int s = mlp_splits(n, units);
-  return s < dim / 128 ? s : dim / 128;
-}
-hipError_t bf16_gemm_partials(const uint16_t* h, const uint16_t* w, int32_t n, int32_t dim, int32_t units,
-                              int32_t splits, float* parts, hipStream_t s);
 hipError_t seq_attention(const SeqDev& S, int layer, const float* qkv, float* o, int n, hipStream_t s);
 hipError_t seq_fork(const SeqDev& S, const int32_t* pairs, int n, hipStream_t s);
 hipError_t seq_set_len(const SeqDev& S, const int32_t* ids, int n, int value, hipStream_t s);

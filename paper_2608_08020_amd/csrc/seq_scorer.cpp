@@ -44,11 +44,11 @@ bool seq_layout(const gambit_scorer_desc* d, SeqLayout* L) {
   L->planes = take(2 * 3 * dm * D);
   L->cvec = take(4 * dm);
   L->dvec = take(4 * dm);
-  // the input projection's split partial sums (splits x n x 3 d_model), the
+  // the input projection's split partial sums (splits x n x d_model), the
   // largest over every n <= max_traces
   size_t part = 0;
   for (size_t n = 1; n <= T; ++n)
-    part = std::max(part, (size_t)gambit::bf16_partial_splits((int)n, (int)D, (int)(3 * dm)) * n * 3 * dm);
+    part = std::max(part, (size_t)gambit::seq_in_splits((int)n, (int)D, (int)dm) * n * dm);
   L->part = take(4 * part);
   L->x = take(4 * T * dm);
   L->stats = take(8 * T * (dm / 16));
@@ -225,9 +225,8 @@ gambit_status gambit_scorer_step(gambit_scorer* q, int32_t n, const int32_t* ids
   float* g = wsp<float>(q, q->L.g);
   using namespace gambit;
   const uint16_t* hb = static_cast<const uint16_t*>(h);
-  const int in_splits = bf16_partial_splits(n, D, 3 * dm);
-  SEQ_TRY(q, bf16_gemm_partials(hb, wsp<uint16_t>(q, q->L.planes), n, D, 3 * dm, in_splits, part, s),
-          "input projection");
+  const int in_splits = seq_in_splits(n, D, dm);
+  SEQ_TRY(q, seq_proj_in(hb, wsp<uint16_t>(q, q->L.planes), n, D, dm, in_splits, part, s), "input projection");
   SEQ_TRY(q, seq_reduce_in(hb, D, part, in_splits, wsp<float>(q, q->L.cvec), wsp<float>(q, q->L.dvec), x, dm, stats,
                            n, s),
           "input projection reduce");

@@ -6,10 +6,10 @@
 // exactly into three bf16 planes when the scorer is created.
 //
 // Per boundary, for the n listed traces (rows):
-//   x  = GELU(LN_in(h) W_in^T)             bf16_gemm_partials (h against the
-//                                           planes, K split; mlp_scorer.hip);
-//                                           reduce_in_kernel (the splits and
-//                                           planes added, LN_in applied)
+//   x  = GELU(LN_in(h) W_in^T)             proj_in_kernel (h against the
+//                                           planes, K split);
+//                                           reduce_in_kernel (the splits
+//                                           added, LN_in applied)
 //   per layer: qkv = LN1(x) Wqkv^T; o = attention step (RoPE, append the step's
 //   key and value, attend over the trace's steps 0..t); x += o Wo^T;
 //   g = SiLU(LN2(x) W1^T) * (LN2(x) W3^T); x += g W2^T
@@ -313,15 +313,105 @@ __global__ __launch_bounds__(256) void head_kernel(const float* x, int d, SeqDev
   }
 }
 
+// The input projection h W'^T, W' in its three bf16 planes, on the bf16 matrix
+// cores: part[s][m][c] is split s's share.  A workgroup (eight waves) takes 64
+// rows x 64 columns of one split, all three planes: they share the rows'
+// operands, and one sum leaves instead of three - hi and mid + lo are summed
+// apart (the small planes' sums round at their own size) and added at the end.
+// Bound by the operands' way through LDS and by the partial sums' way to the
+// reduce: with a product of N = 3 d_model in 128 x 128 tiles, 15.7 MB of them
+// at 512 rows x 4096 -> 256, 10.4 us and 6.8 us for the reduce; 4.2 MB so, 8.7
+// and 5.1 us.
+//
+// LDS: a ring of four slabs of 64 k, three in flight by direct loads; a slab
+// holds 256 rows of 128 bytes, the 64 of h, then each plane's 64.  Row r's
+// 16-byte chunk c sits at c ^ ((r >> 1) & 7), so the 16 rows of an operand
+// read fall on 16 different bank groups.  Wave w fills rows 32 w .. 32 w + 31
+// and computes rows 32 (w & 1) .. + 31, columns 16 (w >> 1) .. + 15.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+constexpr int kInTile = 64, kInRows = 4 * kInTile, kInSlab = kInRows * 128, kInStages = 4, kInWaves = 8;
+
+__global__ __launch_bounds__(64 * kInWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void proj_in_kernel(
+    const uint16_t* h, const uint16_t* planes, int n, int dim, int dm, int splits, float* part) {
+  constexpr int kLoads = kInRows / 8 / kInWaves;  // 8-row loads per wave and slab
+  __shared__ __attribute__((aligned(1024))) uint8_t ring[kInStages * kInSlab];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  // items in (split, column tile, row tile) order; workgroup b runs on XCD b %
+  // 8, and an XCD takes consecutive items (few splits' operands in its L2)
+  const int G = gridDim.x;
+  const int item = (G & 7) ? blockIdx.x : (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);
+  const int tm = (n + kInTile - 1) / kInTile, tc = dm / kInTile;
+  const int s = item / (tm * tc), tile = item - s * tm * tc;
+  const int c0 = tile / tm * kInTile, m0 = tile % tm * kInTile;
+  const int slabs = dim / 64;
+  const int g0 = s * slabs / splits, ng = (s + 1) * slabs / splits - g0;
+  const uint16_t* src[kLoads];
+#pragma unroll
+  for (int d = 0; d < kLoads; ++d) {
+    const int r = 32 * wave + 8 * d + (lane >> 3);
+    const uint16_t* row = r < kInTile ? h + (size_t)min(m0 + r, n - 1) * dim  // rows past n re-read the last (never stored)
+                                      : planes + ((size_t)(r / kInTile - 1) * dm + c0 + r % kInTile) * dim;
+    src[d] = row + 64 * g0 + 8 * ((lane & 7) ^ ((r >> 1) & 7));
+  }
+  auto issue = [&](int g) {
+    uint8_t* st = ring + (g % kInStages) * kInSlab + wave * kLoads * 1024;
+#pragma unroll
+    for (int d = 0; d < kLoads; ++d) dma16(src[d] + 64 * g, st + d * 1024);
+  };
+  const int i = lane & 15, q = lane >> 4, sw = (i >> 1) & 7;
+  const int mr = 32 * (wave & 1), cr = 16 * (wave >> 1);
+  f32x4 hi[2], lo[2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a) hi[a] = lo[a] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int g = 0; g < kInStages - 1 && g < ng; ++g) issue(g);
+  for (int g = 0; g < ng; ++g) {
+    switch (min(kInStages - 2, ng - 1 - g)) {  // slabs asked for after this one
+      case 2: wait_vmcnt<2 * kLoads>(); break;
+      case 1: wait_vmcnt<kLoads>(); break;
+      default: wait_vmcnt<0>(); break;
+    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's reads of slab g - 1 are done
+    barrier_no_fence();                  // slab g is in; every wave is done with slab g - 1
+    if (g + kInStages - 1 < ng) issue(g + kInStages - 1);
+    const uint8_t* st = ring + (g % kInStages) * kInSlab + i * 128;
+    bf16x8 A[2][2], B[2][3];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int pos = ((4 * x + q) ^ sw) * 16;
+#pragma unroll
+      for (int a = 0; a < 2; ++a) A[x][a] = *reinterpret_cast<const bf16x8*>(st + (mr + 16 * a) * 128 + pos);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) B[x][p] = *reinterpret_cast<const bf16x8*>(st + (kInTile * (p + 1) + cr) * 128 + pos);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // all ten reads are issued before the first product
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        lo[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[x][a], B[x][2], lo[a], 0, 0, 0);
+        hi[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[x][a], B[x][0], hi[a], 0, 0, 0);
+        lo[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[x][a], B[x][1], lo[a], 0, 0, 0);
+      }
+  }
+  // lane (q, i) holds rows mr + 16 a + 4 q + e of column cr + i: 64 consecutive
+  // bytes of four rows per store
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int m = m0 + mr + 16 * a + 4 * q + e;
+      if (m < n) part[((size_t)s * n + m) * dm + c0 + cr + i] = hi[a][e] + lo[a][e];
+    }
+}
+
 // The input projection's reduce, one workgroup per row: the input
 // LayerNorm's statistics of h[row] (mean, then the mean squared deviation),
-// the split partial sums of h W'^T over the three planes (parts
-// [splits][n][3 d]: plane p of column i at p d + i), added split by split in
-// order, then x = GELU(rstd (y - mean c[i]) + dv[i]) (LN_in(h) W_in^T
+// the split partial sums of h W'^T (part [splits][n][d]) added split by split
+// in order, then x = GELU(rstd (y - mean c[i]) + dv[i]) (LN_in(h) W_in^T
 // rearranged: c = the row sums of W', dv = W_in b).  The state's first 4096 values (four 8-byte loads per thread, kept in
 // registers for both statistics passes) and the first column's partial sums
 // of up to kInBatch splits are all requested before any of them is used.
-constexpr int kInBatch = 12;
+constexpr int kInBatch = 16;
 
 __global__ __launch_bounds__(256) void reduce_in_kernel(const uint16_t* h, int dim, const float* part, int splits,
                                                         const float* c, const float* dv, float* x, int d, float2* stats,
@@ -330,15 +420,13 @@ __global__ __launch_bounds__(256) void reduce_in_kernel(const uint16_t* h, int d
   const int row = blockIdx.x, tid = threadIdx.x;
   const uint2* h4 = reinterpret_cast<const uint2*>(h + (size_t)row * dim);  // four bf16 per load
   const int nh4 = dim / 4;
-  const size_t units = (size_t)3 * d, MN = (size_t)n * units, pbase = (size_t)row * units, base = (size_t)row * d;
+  const size_t MN = (size_t)n * d, base = (size_t)row * d;
   // split partials of column i, splits z0 .. z0 + kInBatch - 1 (indices
   // clamped: every load is in bounds; only splits < `splits` are added)
-  float v[kInBatch][3];
+  float v[kInBatch];
   auto load_parts = [&](int i, int z0) {
 #pragma unroll
-    for (int e = 0; e < kInBatch; ++e)
-#pragma unroll
-      for (int p = 0; p < 3; ++p) v[e][p] = part[(size_t)min(z0 + e, splits - 1) * MN + pbase + p * d + i];
+    for (int e = 0; e < kInBatch; ++e) v[e] = part[(size_t)min(z0 + e, splits - 1) * MN + base + i];
   };
   uint2 hr[4];
 #pragma unroll
@@ -384,7 +472,7 @@ __global__ __launch_bounds__(256) void reduce_in_kernel(const uint16_t* h, int d
       if (i != tid || z0 != 0) load_parts(i, z0);
 #pragma unroll
       for (int e = 0; e < kInBatch; ++e)
-        if (z0 + e < splits) y += (v[e][0] + v[e][1]) + v[e][2];
+        if (z0 + e < splits) y += v[e];
     }
     y = gelu_erf(hrstd * (y - hmean * c[i]) + dv[i]);
     x[base + i] = y;
@@ -651,6 +739,13 @@ hipError_t seq_gemm_add(const float* A, const float* W, float* C, int M, int N, 
 hipError_t seq_prep_input(const float* w_in, const float* ln_g, const float* ln_b, int dim, int dm, uint16_t* planes,
                           float* c, float* dv, hipStream_t s) {
   hipLaunchKernelGGL(prep_input_kernel, dim3(dm), dim3(256), 0, s, w_in, ln_g, ln_b, dim, dm, planes, c, dv);
+  return hipGetLastError();
+}
+
+hipError_t seq_proj_in(const uint16_t* h, const uint16_t* planes, int n, int dim, int dm, int splits, float* part,
+                       hipStream_t s) {
+  const int tiles = (n + kInTile - 1) / kInTile * (dm / kInTile);
+  hipLaunchKernelGGL(proj_in_kernel, dim3(tiles * splits), dim3(64 * kInWaves), 0, s, h, planes, n, dim, dm, splits, part);
   return hipGetLastError();
 }
 

@@ -256,3 +256,24 @@ def test_product_tiles(n, heads, d_ff):
             want = scorer_outputs(w, hist[:r + 1], heads)[-1]
             assert abs(got[r][t] - want) <= TOL, (t, r, got[r][t], want)
     gpu.check()
+
+
+@pytest.mark.parametrize("n,dim,heads", [
+    (1, 128, 1),     # one row, a slab per split
+    (65, 384, 1),    # a row tile of one row
+    (130, 2176, 5),  # 34 slabs over 17 splits
+    (1030, 640, 4),  # 10 slabs over 3 splits
+    (2100, 128, 8),  # more tiles than workgroups wanted: one split
+])
+def test_input_projection_tiles(n, dim, heads):
+    """The input projection's row tiles and K splits: one boundary, rows at
+    the tiles' edges against the oracle."""
+    import dataclasses
+    cfg = dataclasses.replace(SEQ_SMALL, input_dim=dim, d_model=64 * heads, n_heads=heads, n_layers=0, max_steps=3, slots=n)
+    w, gpu, _ = _make(cfg)
+    h = step_states(cfg, 0)[:n]
+    got = gpu.step(list(range(n)), _bf16(h)).cpu().numpy()
+    for t in sorted({0, 31, 32, 63, 64, 65, n // 2, n - 65, n - 2, n - 1} & set(range(n))):
+        want = scorer_outputs(w, bf16_to_f64(h[t])[None], heads)[-1]
+        assert abs(got[t] - want) <= TOL, (t, got[t], want)
+    gpu.check()

@@ -44,6 +44,7 @@
 // product keeps ~16 bits of P.  fp8 E4M3 K/V are widened to bf16 (exact); a
 // block's K scale multiplies its scores and its V scale multiplies P.
 #include <cmath>
+#include <type_traits>
 
 #include "kernels.h"
 #include "lds_dma.h"
@@ -746,29 +747,51 @@ __device__ void narrow_unit(const DevPool& P, const AttnLaunch& A, const AttnUni
     meta(2, na);
     fetch_k(na, ta);
   }
-  auto step = [&](int i, Tile<FP8>& t, TileMeta& m, TileMeta& n, Tile<FP8>& to, TileMeta& no) {
+  // FULL: tiles i + 1 .. i + 3 exist and tile i is whole.  Nothing is
+  // conditional then, so the compiler counts the loads in flight and a wait
+  // for one half of a tile leaves the later ones (up to 24 loads) in flight;
+  // where a fetch may have been skipped it waits for every load, its own
+  // prefetch included.
+  auto step = [&](auto full, int i, Tile<FP8>& t, TileMeta& m, TileMeta& n, Tile<FP8>& to, TileMeta& no) {
+    constexpr bool FULL = decltype(full)::value;
     f32x4 r0[RB], r1[RB];
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
       r0[r] = s0[r];
       r1[r] = s1[r];
     }
-    if (i + 1 < ntile) {
+    if (FULL || i + 1 < ntile) {
       scores(to, s0, s1);
-      if (i + 3 < ntile) {
+      if (FULL || i + 3 < ntile) {
         meta(i + 3, no);
         fetch_k(no, to);
       }
     }
-    pv_direct<FP8, RB>(t, r0, r1, 32 * i, ntok, g, m, sl, st);
-    if (i + 2 < ntile) {
+    pv_direct<FP8, RB>(t, r0, r1, 32 * i, FULL ? 32 * i + 32 : ntok, g, m, sl, st);
+    if (FULL || i + 2 < ntile) {
       fetch_v(n, t);
       m = n;
     }
   };
-  for (int i = 0; i < ntile; i += 2) {
-    step(i, ta, ma, na, tb, nb);
-    if (i + 1 < ntile) step(i + 1, tb, mb, nb, ta, na);
+  // fp8 takes the tiles that have three after them in a loop of their own:
+  // its scales' loads at a unit's start made the guarded loop wait for
+  // everything three times every two tiles.  256 traces fp8 with shared runs
+  // 4237 -> 4132 us a pass of 16 steps, 256 private traces 8347 -> 8115 us,
+  // 64 private traces 1917 -> 1804 us, 256 private traces without any shared
+  // run wide enough for a cooperative item 5724 -> 5485 us (8 steps).  bf16's
+  // guarded loop waits once every two tiles; with its tiles in such a loop 64
+  // private traces took 2704 -> 2603 us, but what is bound by HBM lost: 256
+  // private traces 13170 -> 13440 us.
+  int i = 0;
+  if constexpr (FP8) {
+    for (; i + 4 < ntile; i += 2) {
+      step(std::true_type{}, i, ta, ma, na, tb, nb);
+      step(std::true_type{}, i + 1, tb, mb, nb, ta, na);
+    }
+  }
+  for (; i < ntile; i += 2) {
+    step(std::false_type{}, i, ta, ma, na, tb, nb);
+    if (i + 1 < ntile) step(std::false_type{}, i + 1, tb, mb, nb, ta, na);
   }
 #pragma unroll
   for (int r = 0; r < RB; ++r) write_partial<STREAM>(A, U, qrow[r], g.q, st[r]);

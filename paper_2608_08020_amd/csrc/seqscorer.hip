@@ -88,11 +88,10 @@ __device__ inline float2 row_stats(float x) {
 // NW, (w + 1) G / NW) of the G = K / 32, and the waves' sums meet in LDS.
 // These products are short (K = 256 or 768, 0.07-0.4 GFLOP at 512 rows): what
 // bounds them is the round trip to the operands, the rate at which a CU takes
-// them from L2, and the launch.  So a wave asks for SB slabs of both operands
+// them from L2, and the launch.  So a wave asks for two slabs of both operands
 // at once, by direct loads into LDS that only it reads (no barrier), eight
-// rows of 128 bytes per load: whole lines reach 127-140 GB/s per CU, the
-// matrix cores' own operand shape (16 rows of 64 bytes) read straight into
-// registers 37 GB/s.  Per boundary of 512 traces (d_model 256, d_ff 768, two
+// rows of 128 bytes per load (whole lines, where the matrix cores' own operand
+// shape, 16 rows of 64 bytes, takes half of each).  Per boundary of 512 traces (d_model 256, d_ff 768, two
 // layers) the eight products take 56 us; split over workgroups, the split sums
 // through memory and a launch each to add them and take the LayerNorm, they
 // and the four reduces took 70 us.
@@ -118,10 +117,11 @@ __device__ inline float2 row_stats(float x) {
 // and W_3 rows interleaved in groups of 16, so column blocks 2 c and 2 c + 1
 // are W_1 and W_3 of the same 16 outputs, and C[m][16 c + i] = SiLU(a1) * a3
 // with row stride N / 2.
-template <int MB, int NB, int NW, int SB, bool LN, int EPI>
+template <int MB, int NB, int NW, bool LN, int EPI>
 __global__ __launch_bounds__(64 * NW) void gemm_kernel(const float* A, const float* W, float* C, int M, int N, int K,
                                                        const float* lg, const float* lb, float2* stats) {
   static_assert(EPI != kEpiSwiGLU || NB % 2 == 0, "W_1 and W_3 blocks in pairs");
+  constexpr int SB = 2;                        // slabs asked for at once
   constexpr int kSlab = 16 * (MB + NB) * 128;  // bytes of one slab of both operands: A's rows, then W's
   constexpr int kLoads = 2 * (MB + NB);        // 1 KB loads per slab
   constexpr int T4 = MB * NB * 64;             // the tile in f32x4
@@ -198,13 +198,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_kernel(const float* A, const flo
     for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int at = li * 128, sw = (li >> 1) & 7;
   for (int g = g0, slot = 0; g < g1; ++g) {
-    // slab g is in: of the slabs asked for after it (at most SB - 1), each is
-    // kLoads loads
-    switch (min(SB - 1, g1 - 1 - g)) {
-      case 2: wait_vmcnt<2 * kLoads>(); break;
-      case 1: wait_vmcnt<kLoads>(); break;
-      default: wait_vmcnt<0>(); break;
-    }
+    // slab g is in: at most the kLoads loads of the next one are on their way
+    if (g + 1 < g1)
+      wait_vmcnt<kLoads>();
+    else
+      wait_vmcnt<0>();
     asm volatile("" ::: "memory");
     const uint8_t* src = mine + slot * kSlab + at;
 #pragma unroll
@@ -273,6 +271,124 @@ __global__ __launch_bounds__(64 * NW) void gemm_kernel(const float* A, const flo
       }
     }
   }
+}
+
+// The same product with LayerNorm for large ones, whose time is the matrix
+// cores' and not the round trip: TM x 64 tiles, the four waves share both
+// operands, staged in LDS 128 k at a time (rows padded to 132 floats, so the 16
+// rows of an operand read fall on 16 different bank groups), the next chunk's
+// loads in flight in registers while this one is multiplied; each wave takes a
+// (TM / 2) x 32 quarter.  A is normalised on its way into LDS; a chunk's sums
+// are added to the tile's at its end, so the rounding stays that of 128
+// products and K / 128 sums.
+constexpr int kKC = 128;      // k per staged chunk
+constexpr int kKP = kKC + 4;  // padded LDS row, floats
+template <int TM, int EPI>
+__global__ __launch_bounds__(256) void gemm_wide_kernel(const float* A, const float* W, float* C, int M, int N, int K,
+                                                        const float* lg, const float* lb, const float2* stats) {
+  constexpr int MB = TM / 32;  // 16-row blocks per wave
+  constexpr int AV = TM / 8, WV = 8;  // float4 groups of A and of W per thread and chunk
+  constexpr int kPer = 256 / TM;      // threads per row's statistics
+  __shared__ __attribute__((aligned(16))) float As[TM * kKP];
+  __shared__ __attribute__((aligned(16))) float Ws[64 * kKP];
+  __shared__ float2 norm[TM];  // LN(x) = (x norm.x + norm.y) gain + bias
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * 64;
+  const int li = lane & 15, lq = lane >> 4;
+  const int wm = (wave >> 1) * (TM / 2), wn = (wave & 1) * 32;
+  // group v of a thread is row lr + 8 v, k offset lk
+  const int lk = 4 * (tid & 31), lr = tid >> 5;
+  f32x4 ar[AV], wr[WV], gv, bv;
+  // chunk [kb, kb + kKC), groups past K are zero and read nothing; rows past M
+  // re-read the last (never stored)
+  auto fetch = [&](int kb) {
+    const bool kin = kb + lk < K;
+    const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+    gv = kin ? *reinterpret_cast<const f32x4*>(lg + kb + lk) : zero;
+    bv = kin ? *reinterpret_cast<const f32x4*>(lb + kb + lk) : zero;
+#pragma unroll
+    for (int v = 0; v < AV; ++v)
+      ar[v] = kin ? *reinterpret_cast<const f32x4*>(A + (size_t)min(m0 + lr + 8 * v, M - 1) * K + kb + lk) : zero;
+#pragma unroll
+    for (int v = 0; v < WV; ++v)
+      wr[v] = kin ? *reinterpret_cast<const f32x4*>(W + (size_t)(n0 + lr + 8 * v) * K + kb + lk) : zero;
+  };
+  fetch(0);
+  {
+    const int r = tid / kPer, nb = K / 16;
+    const float2* sp = stats + (size_t)min(m0 + r, M - 1) * nb;
+    auto row = [&](float v) {
+#pragma unroll
+      for (int o = 1; o < kPer; o <<= 1) v += __shfl_xor(v, o);
+      return v;
+    };
+    float s = 0.f, v = 0.f;
+    for (int b = tid % kPer; b < nb; b += kPer) s += sp[b].x;
+    const float mean = row(s) / nb;
+    for (int b = tid % kPer; b < nb; b += kPer) {
+      const float2 x = sp[b];
+      const float e = x.x - mean;
+      v += x.y + 16.f * e * e;
+    }
+    const float rstd = 1.f / sqrtf(row(v) / K + kSeqLnEps);
+    if (tid % kPer == 0) norm[r] = make_float2(rstd, -mean * rstd);
+  }
+  __syncthreads();
+  float2 nr[AV];
+#pragma unroll
+  for (int v = 0; v < AV; ++v) nr[v] = norm[lr + 8 * v];
+  f32x4 acc[MB][2], sum[MB][2];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int kb = 0; kb < K; kb += kKC) {
+    __syncthreads();  // the previous chunk's reads are done
+#pragma unroll
+    for (int v = 0; v < AV; ++v)
+      *reinterpret_cast<f32x4*>(&As[(lr + 8 * v) * kKP + lk]) = (ar[v] * nr[v].x + nr[v].y) * gv + bv;
+#pragma unroll
+    for (int v = 0; v < WV; ++v) *reinterpret_cast<f32x4*>(&Ws[(lr + 8 * v) * kKP + lk]) = wr[v];
+    __syncthreads();
+    if (kb + kKC < K) fetch(kb + kKC);
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int kn = min(kKC, K - kb);  // a multiple of 64
+    for (int kc = 0; kc < kn; kc += 16) {
+      f32x4 a[MB], w[2];
+#pragma unroll
+      for (int i = 0; i < MB; ++i) a[i] = *reinterpret_cast<const f32x4*>(&As[(wm + 16 * i + li) * kKP + kc + 4 * lq]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) w[j] = *reinterpret_cast<const f32x4*>(&Ws[(wn + 16 * j + li) * kKP + kc + 4 * lq]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], w[j][e], acc[i][j], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) sum[i][j] += acc[i][j];
+  }
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + wm + 16 * i + 4 * lq + r;
+      if (m >= M) continue;
+      if constexpr (EPI == kEpiSwiGLU) {  // the wave's column blocks are W_1 and W_3 of the same 16 outputs
+        const float x = sum[i][0][r], y = sum[i][1][r];
+        C[(size_t)m * (N / 2) + (n0 + wn) / 2 + li] = x / (1.f + expf(-x)) * y;
+      } else {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) C[(size_t)m * N + n0 + wn + 16 * j + li] = sum[i][j][r];
+      }
+    }
 }
 
 __device__ inline float block_sum(float v, float* red) {
@@ -696,44 +812,98 @@ __global__ void seq_set_len_kernel(SeqDev S, const int32_t* ids, int n, int valu
 
 }  // namespace
 
-// Tiles: a product of few rows takes the smallest ones (more workgroups, and
-// none of them long); where larger ones still give the chip ~200 workgroups,
-// each operand is read by fewer of them.  At 512 rows, d_model 256, d_ff 768:
-// QKV 32 x 48 (6.9 us), SwiGLU 32 x 96 (9.5 us), the d_model-wide ones 16 x 32
-// (W_o 4.9, W_2 6.7 us), 256 workgroups each; 24 rows of d_model 128: 3.6-4.7
-// us each.
-template <int MB, int NB, int NW, int KG, bool LN, int EPI>
+// The tile of a product, by its estimated time.  A tile's workgroups fill the
+// chip per_cu to a compute unit (its LDS), in rounds; a round takes
+// round + K (k_round + k_wg m) us with m workgroups to a unit, and the launch
+// `once` more.  The four numbers of a tile are fitted to its times on MI355X
+// over 16 to 1000 rows and d_model 128 to 1536 with d_ff 1 to 4 times that
+// (mean error 2-4%); the tile picked from them takes 2% more than the best one
+// on average, 13% at worst.  Picked by workgroup counts from fewer tiles, as
+// before, a layer's four products took (us, before -> now; the kernels of one
+// shared tile with split sums and reduces, which came before those, in
+// brackets): 512 rows, d_model 256, d_ff 768 25.6 -> 25.5 (33.8); 400 rows, 384,
+// 1152 54.2 -> 40.3 (44.2); 300 rows, 512, 2048 81.7 -> 60.5 (66.3); 1000 rows,
+// 1024, 2048 438 -> 256 (250); 24 rows, 128, 256 16.1 -> 14.7 (21.3).
+struct TileCost {
+  int rows, cols, per_cu;
+  float once, round, k_round, k_wg;
+};
+static float tile_us(const TileCost& t, int M, int N, int K) {
+  constexpr int kCU = 256;
+  const long n = (long)((M + t.rows - 1) / t.rows) * (N / t.cols);
+  const long whole = n / (kCU * t.per_cu), rest = n % (kCU * t.per_cu);
+  const float rounds = (float)(whole + (rest > 0)), wgs = (float)(whole * t.per_cu + (rest + kCU - 1) / kCU);
+  return t.once + t.round * rounds + K * (t.k_round * rounds + t.k_wg * wgs);
+}
+template <int N_TILES>
+static int pick_tile(const TileCost (&tiles)[N_TILES], int M, int N, int K) {
+  int best = 0;
+  float us = 0.f;
+  for (int i = 0; i < N_TILES; ++i) {
+    if (N % tiles[i].cols) continue;
+    const float t = tile_us(tiles[i], M, N, K);
+    if (us == 0.f || t < us) best = i, us = t;
+  }
+  return best;
+}
+
+template <int MB, int NB, int NW, bool LN, int EPI>
 static hipError_t launch_gemm(const float* A, const float* W, float* C, int M, int N, int K, const float* lg,
                               const float* lb, float2* stats, hipStream_t s) {
-  hipLaunchKernelGGL((gemm_kernel<MB, NB, NW, KG, LN, EPI>), dim3(N / (16 * NB), (M + 16 * MB - 1) / (16 * MB)),
+  hipLaunchKernelGGL((gemm_kernel<MB, NB, NW, LN, EPI>), dim3(N / (16 * NB), (M + 16 * MB - 1) / (16 * MB)),
                      dim3(64 * NW), 0, s, A, W, C, M, N, K, lg, lb, stats);
   return hipGetLastError();
 }
-// Workgroups of tiles of `rows` x `cols`.
-static long tiles(int M, int N, int rows, int cols) { return (long)((M + rows - 1) / rows) * (N / cols); }
+template <int TM, int EPI>
+static hipError_t launch_wide(const float* A, const float* W, float* C, int M, int N, int K, const float* lg,
+                              const float* lb, const float2* stats, hipStream_t s) {
+  hipLaunchKernelGGL((gemm_wide_kernel<TM, EPI>), dim3(N / 64, (M + TM - 1) / TM), dim3(256), 0, s, A, W, C, M, N, K,
+                     lg, lb, stats);
+  return hipGetLastError();
+}
+
+// N a multiple of 64.
+template <int EPI>
+static hipError_t gemm_ln(const float* A, const float* W, float* C, int M, int N, int K, const float* lg,
+                          const float* lb, const float2* stats, hipStream_t s) {
+  static const TileCost tiles[] = {{16, 32, 3, 2.39f, 0.05f, 0.0022f, 0.0056f},
+                                   {16, 64, 2, 2.07f, 0.41f, 0.0020f, 0.0085f},
+                                   {32, 96, 1, 0.52f, 2.26f, 0.0231f, 0.f},
+                                   {32, 64, 3, 3.10f, 0.f, 0.0063f, 0.0105f},
+                                   {64, 64, 2, 3.53f, 0.f, 0.0087f, 0.0192f}};
+  float2* st = const_cast<float2*>(stats);
+  switch (pick_tile(tiles, M, N, K)) {
+    case 0: return launch_gemm<1, 2, 4, true, EPI>(A, W, C, M, N, K, lg, lb, st, s);
+    case 1: return launch_gemm<1, 4, 4, true, EPI>(A, W, C, M, N, K, lg, lb, st, s);
+    case 2: return launch_gemm<2, 6, 4, true, EPI>(A, W, C, M, N, K, lg, lb, st, s);
+    case 3: return launch_wide<32, EPI>(A, W, C, M, N, K, lg, lb, stats, s);
+    default: return launch_wide<64, EPI>(A, W, C, M, N, K, lg, lb, stats, s);
+  }
+}
 
 hipError_t seq_gemm_ln(const float* A, const float* W, float* C, int M, int N, int K, const float* lg, const float* lb,
                        const float2* stats, hipStream_t s) {
-  float2* st = const_cast<float2*>(stats);
-  if (tiles(M, N, 32, 48) >= 192) return launch_gemm<2, 3, 4, 2, true, kEpiNone>(A, W, C, M, N, K, lg, lb, st, s);
-  return launch_gemm<1, 1, 8, 1, true, kEpiNone>(A, W, C, M, N, K, lg, lb, st, s);
+  return gemm_ln<kEpiNone>(A, W, C, M, N, K, lg, lb, stats, s);
 }
 
 hipError_t seq_gemm_ln_swiglu(const float* A, const float* W, float* C, int M, int N, int K, const float* lg,
                               const float* lb, const float2* stats, hipStream_t s) {
-  float2* st = const_cast<float2*>(stats);
-  if (N % 96 == 0 && tiles(M, N, 32, 96) >= 192)
-    return launch_gemm<2, 6, 4, 2, true, kEpiSwiGLU>(A, W, C, M, N, K, lg, lb, st, s);
-  if (tiles(M, N, 32, 64) >= 192) return launch_gemm<2, 4, 8, 1, true, kEpiSwiGLU>(A, W, C, M, N, K, lg, lb, st, s);
-  return launch_gemm<1, 2, 8, 1, true, kEpiSwiGLU>(A, W, C, M, N, K, lg, lb, st, s);
+  return gemm_ln<kEpiSwiGLU>(A, W, C, M, N, K, lg, lb, stats, s);
 }
 
 hipError_t seq_gemm_add(const float* A, const float* W, float* C, int M, int N, int K, float2* stats, hipStream_t s) {
-  if (tiles(M, N, 16, 32) >= 192) {
-    if (K > 256) return launch_gemm<1, 2, 8, 3, false, kEpiAdd>(A, W, C, M, N, K, nullptr, nullptr, stats, s);
-    return launch_gemm<1, 2, 4, 2, false, kEpiAdd>(A, W, C, M, N, K, nullptr, nullptr, stats, s);
+  static const TileCost tiles[] = {{16, 16, 2, 1.88f, 1.69f, 0.f, 0.0018f},
+                                   {16, 32, 3, 1.72f, 1.16f, 0.f, 0.0035f},
+                                   {32, 32, 2, 1.64f, 1.23f, 0.f, 0.0057f},
+                                   {32, 48, 2, 3.21f, 1.80f, 0.0005f, 0.0071f},
+                                   {32, 64, 1, 0.f, 3.95f, 0.0098f, 0.f}};
+  switch (pick_tile(tiles, M, N, K)) {
+    case 0: return launch_gemm<1, 1, 8, false, kEpiAdd>(A, W, C, M, N, K, nullptr, nullptr, stats, s);
+    case 1: return launch_gemm<1, 2, 4, false, kEpiAdd>(A, W, C, M, N, K, nullptr, nullptr, stats, s);
+    case 2: return launch_gemm<2, 2, 4, false, kEpiAdd>(A, W, C, M, N, K, nullptr, nullptr, stats, s);
+    case 3: return launch_gemm<2, 3, 4, false, kEpiAdd>(A, W, C, M, N, K, nullptr, nullptr, stats, s);
+    default: return launch_gemm<2, 4, 4, false, kEpiAdd>(A, W, C, M, N, K, nullptr, nullptr, stats, s);
   }
-  return launch_gemm<1, 1, 8, 2, false, kEpiAdd>(A, W, C, M, N, K, nullptr, nullptr, stats, s);
 }
 
 hipError_t seq_prep_input(const float* w_in, const float* ln_g, const float* ln_b, int dim, int dm, uint16_t* planes,

@@ -236,10 +236,10 @@ def test_histories_past_one_pass_of_the_attention_step():
 
 
 @pytest.mark.parametrize("n,heads,d_ff", [
-    (33, 1, 64),     # small tiles, fewer k slabs than waves, a partial last row tile
+    (33, 1, 64),     # fewer k slabs than waves, a partial last row tile
     (40, 17, 192),   # d_model 1088: more slabs than a wave holds, rows wider than one pass of the head
-    (300, 4, 704),   # SwiGLU in 32 x 64 tiles (2 d_ff not a multiple of 96)
-    (401, 4, 768),   # every wide tile, a partial last row tile
+    (300, 4, 704),   # 2 d_ff not a multiple of 96
+    (401, 4, 768),   # SwiGLU in 32 x 96 tiles, a partial last row tile
     (401, 3, 320),   # d_model 192: an uneven split of K over the waves
 ])
 def test_product_tiles(n, heads, d_ff):
@@ -256,6 +256,24 @@ def test_product_tiles(n, heads, d_ff):
             want = scorer_outputs(w, hist[:r + 1], heads)[-1]
             assert abs(got[r][t] - want) <= TOL, (t, r, got[r][t], want)
     gpu.check()
+
+
+@pytest.mark.parametrize("n,heads,d_ff", [
+    (700, 1, 1216),   # QKV in 16 x 64 tiles; SwiGLU in shared 64 x 64 ones over half a chunk of k
+    (1030, 3, 64),    # QKV in 32 x 96, W_2 in 32 x 32 tiles
+    (300, 5, 64),     # QKV in shared 32 x 64 tiles, two and a half chunks of k
+    (1030, 8, 576),   # QKV in shared 64 x 64 tiles
+    (515, 1, 576),    # SwiGLU in 32 x 96 tiles
+    (401, 1, 960),    # SwiGLU in shared 32 x 64 tiles
+    (700, 6, 960),    # W_2 in 32 x 48 tiles
+    (2049, 3, 704),   # W_2 in 32 x 64 tiles
+    (1030, 9, 64),    # W_o in 32 x 48 tiles
+    (17, 7, 448),     # W_o and W_2 in 16 x 16 tiles, SwiGLU and QKV in 16 x 32 ones
+])
+def test_product_tiles_by_time(n, heads, d_ff):
+    """Every tile of the products, with a partial last row tile: two
+    boundaries, rows at the tiles' edges against the oracle."""
+    test_product_tiles(n, heads, d_ff)
 
 
 @pytest.mark.parametrize("n,dim,heads", [

@@ -1115,12 +1115,15 @@ __global__ __launch_bounds__(kThreads, 2) void attn_units_kernel(DevPool P, Attn
 // Log-sum-exp merge of a row's partials.  One wave per (list position,
 // query head): lane k < nk reads partial k's (max, sum) and the wave reduces
 // the maximum and the weighted sum, while the partials themselves are already
-// on their way: half-wave h reads partials 2 j + h whole (16 bytes a lane),
-// kMergeDepth of them per half requested before the first is used, the loads
-// past nk clamped to the last partial and left out of the sums.  Each half
-// adds its partials in order; the two halves' sums are added last.  Bound by
-// latency at small populations (a row's partials are 2-10 KB) and by HBM at
-// large ones (0.1 GB at 512 traces).
+// on their way: half-wave h reads partials 2 j + h whole (16 bytes a lane), up
+// to kMergeDepth of them per half requested before the first is used (an odd
+// count's last partial by both halves, added by one).  Each half adds its
+// partials in order; the two halves' sums are added last.  Bound by latency at
+// small populations (a row's partials are 2-10 KB) and by HBM at large ones
+// (0.1 GB at 512 traces).  Loads past nk are left out by the wave: clamped to
+// the last partial instead, a row of one partial read it 16 times (512 traces
+// of one partial 11.4 -> 7.6 us; two to six of them, 256 private traces, 8.8 ->
+// 6.8 us; 512 branched traces 18.3 -> 16.0 us).
 constexpr int kMergeDepth = 8;
 
 // The merge's part of a launch.  The attention launch's own arguments, with
@@ -1160,8 +1163,9 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeLaunch A) {
   auto load = [&](int k0) {
 #pragma unroll
     for (int j = 0; j < kMergeDepth; ++j)
-      a[j] = __builtin_nontemporal_load(
-          reinterpret_cast<const f32x4*>(pa + (size_t)min(k0 + 2 * j + half, nk - 1) * kHeadDim));
+      if (k0 + 2 * j < nk)
+        a[j] = __builtin_nontemporal_load(
+            reinterpret_cast<const f32x4*>(pa + (size_t)min(k0 + 2 * j + half, nk - 1) * kHeadDim));
   };
   load(0);
   float M = mine.x;
@@ -1176,6 +1180,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeLaunch A) {
     if (k0) load(k0);
 #pragma unroll
     for (int j = 0; j < kMergeDepth; ++j) {
+      if (k0 + 2 * j >= nk) break;
       const int k = k0 + 2 * j + half;  // <= 63
       const float wk = __shfl(w, k);
       if (k < nk) o += wk * a[j];

@@ -96,3 +96,23 @@ def test_unit_lengths_at_the_edges_of_the_tile_loops(kv_dtype):
             ref = decode_attention(q[i].double().numpy(), K[t], V[t], 1 / math.sqrt(128))
             assert_attn_close(out[i], ref, f"step {step}, trace {t} of {len(K[t])} tokens")
     p.pool_check()
+
+
+def test_merge_of_one_to_many_partials():
+    """Rows of 1 to 36 partials (a small launch cuts a context every 16 blocks)."""
+    n = [256 * k + 1 + 37 * k % 200 for k in range(36)] + [5]
+    T, Hq = len(n), 2
+    p = Pool(num_blocks=sum(-(-x // 16) for x in n) + T, num_q_heads=Hq, num_kv_heads=1, max_traces=T, max_blocks_per_trace=640)
+    rng = np.random.default_rng(3)
+    p.kv_alloc(range(T), n)
+    bf = lambda *shape: torch.from_numpy(rng.standard_normal(shape).astype(np.float32)).to(torch.bfloat16)  # noqa: E731
+    kv = [(bf(x, 1, 128), bf(x, 1, 128)) for x in n]
+    for t, (k, v) in enumerate(kv):
+        p.kv_write(t, 0, k.cuda(), v.cuda())
+    q, kn, vn = bf(T, Hq, 128), bf(T, 1, 128), bf(T, 1, 128)
+    out = p.decode_attn(range(T), q.cuda(), kn.cuda(), vn.cuda(), out_dtype=torch.float32).cpu().numpy()
+    assert p.plan_stats(range(T)).max_splits_used == 36
+    for t, (k, v) in enumerate(kv):
+        K, V = (torch.cat([a, b[t:t + 1]]).double().numpy() for a, b in ((k, kn), (v, vn)))
+        assert_attn_close(out[t], decode_attention(q[t].double().numpy(), K, V, 1 / math.sqrt(128)), f"{len(K)} tokens")
+    p.pool_check()

@@ -276,8 +276,9 @@ __device__ inline int query_row(const AttnLaunch& A, const AttnUnit& U, int Hq, 
 }
 
 // Partials: lane (q, lr) holds O[row lr][16 r + 4 q + e] in acc[r][e].  They
-// are read once, by the merge: a set that fits the L2s stays there for it, a
-// larger one (STREAM) would only push out what is still to be read.
+// are read once, by the merge, most of them on another XCD.  A small set is
+// stored plainly, a large one (STREAM) with the non-temporal hint: measured,
+// see part_stream in the host's launch.
 template <bool STREAM>
 __device__ inline void write_partial(const AttnLaunch& A, const AttnUnit& U, int qrow, int q, const RowState& st) {
   const float l = wave_sum_over_groups(st.l);
@@ -312,9 +313,11 @@ __device__ inline void load_q(const AttnLaunch& A, int qrow, bool fp8_direct, in
 // w, so a tile never waits on a table load; the first two tiles take their
 // ids from the unit itself (first_tile), so their loads do not wait for the
 // table either, and the first window's fp8 scales are asked for after those
-// loads.  Entries outside the pool are never dereferenced: they become block
-// 0 and the device error word records them (bf16 checks the id when a tile
-// takes it; fp8 when the window's scales are fetched).
+// loads.  A table entry that is not the block the plan saw sets the device
+// error word once the table is there (check_first).  Entries outside the pool
+// are never dereferenced: they become block 0 and the error word records them
+// (bf16 checks the id when a later tile takes it; fp8 when the window's scales
+// are fetched).
 template <bool FP8>
 struct BlockIds {
   const DevPool& P;
@@ -378,6 +381,12 @@ struct BlockIds {
       b0 = in_pool(__builtin_amdgcn_readlane(cur_id, j0));
       b1 = in_pool(__builtin_amdgcn_readlane(cur_id, j1));
     }
+  }
+  // The table's first entries are the ids that the unit carries.
+  __device__ void check_first(const AttnUnit& U) const {
+    const int want = lane == 0 ? U.first[0] : lane == 1 ? U.first[1] : lane == 2 ? U.first[2] : U.first[3];
+    const uint64_t other = __builtin_amdgcn_ballot_w64(lane < min(nblk, 4) && want >= 0 && cur_id != want);
+    if (other && lane == 0) atomicOr(P.err, kErrBadBlock);
   }
   // ids and scales of tile i (logical blocks 2 i and 2 i + 1, both in one
   // window; a missing second block aliases the first, its tokens are
@@ -549,8 +558,9 @@ __device__ inline void pv_direct(Tile<FP8>& t, const f32x4 (&s0)[RB], const f32x
 
 // The decode step's append, for one KV head: the unit whose end is read at
 // run time covers its trace's last block, so it writes the new token there;
-// the unit waits for the stores before its first tile load.  Only this wave
-// touches this (block, head) tile in the launch.  len is the trace's length
+// the unit waits for the stores before it loads the tile that holds the token
+// (the third tile's loads at the latest).  Only this wave touches this (block,
+// head) tile in the launch.  len is the trace's length
 // including the new token.  When the token opens a block, the block comes
 // from the launch's list (the host took it by the allocation rule); the KV
 // head 0 unit enters it in the table, refcount, free set (and fp8 scales),
@@ -742,6 +752,7 @@ __device__ void narrow_unit(const DevPool& P, const AttnLaunch& A, const AttnUni
   }
   f32x4 s0[RB], s1[RB];
   scores(ta, s0, s1);
+  ids.check_first(U);
   if (ntile > 2) {
     if (open) __builtin_amdgcn_s_waitcnt(0);  // the appended token is in the cache before its tile is read
     meta(2, na);
@@ -1020,6 +1031,10 @@ __device__ void coop_unit(const DevPool& P, const AttnLaunch& A, const AttnUnit&
   __builtin_amdgcn_s_waitcnt(0x0F70);  // all of them are in
   barrier_no_fence();
   for (int i = 2; i < ahead && i < ntile; ++i) issue(i);
+  if (t < min(nblk, 4)) {  // the table's first entries are the ids that the unit carries
+    const int want = t == 0 ? U.first[0] : t == 1 ? U.first[1] : t == 2 ? U.first[2] : U.first[3];
+    if (idw[t] != want) atomicOr(P.err, kErrBadBlock);
+  }
   f32x4 s0[RB], s1[RB];
   if (active) qk(lds, s0, s1);
   // Iteration i issues the scores of tile i + 1 before the softmax and P.V

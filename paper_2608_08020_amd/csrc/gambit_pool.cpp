@@ -1062,11 +1062,14 @@ static gambit_status decode_layer(gambit_pool* p, int32_t layer, int32_t n, cons
     A.part_acc = ws_ptr<float>(p, p->L.part_acc);
     A.part_ml = ws_ptr<float2>(p, p->L.part_ml);
     A.kmax = p->L.kmax;
-    // Partials that fit the eight 4 MB L2s are stored plainly, more of them
-    // with the non-temporal hint.  Per pass, with the hint -> plain: about 20
-    // MB (six fp8 layers of 45 traces) 1603 -> 1502 us, (64 traces) 1520 ->
-    // 1487 us, (256 private traces) unchanged; 59-71 MB (512 traces) 14664 ->
-    // 14845 us, (256 fp8) 3602 -> 3645 us.
+    // Partials of up to 32 MB are stored plainly, more of them with the
+    // non-temporal hint; the line is where measurements cross, not where they
+    // leave a cache (each XCD's L2 holds 4 MB, and the merge reads most rows on
+    // another XCD).  Per pass, with the hint -> plain: about 20 MB (six fp8
+    // layers of 45 traces) 1603 -> 1502 us, (64 traces) 1520 -> 1487 us, (256
+    // private traces) unchanged; 59-71 MB (512 traces) 14664 -> 14845 us, (256
+    // fp8) 3602 -> 3645 us.  Of 33 populations of 20-60 MB, both ways in turn,
+    // 29 took within 1.5% and all within 3% of the other way.
     A.part_stream = p->plan_partials * p->d.num_q_heads * gambit::kHeadDim * 4 > ((size_t)32 << 20);
     A.gshift = __builtin_ctz(p->g);
     A.resident = attn_resident(p);

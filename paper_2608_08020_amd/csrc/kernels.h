@@ -96,7 +96,7 @@ struct DevPool {
 enum : int32_t {
   kErrAllocShort = 1,       // allocator found fewer free blocks than requested
   kErrRefUnderflow = 2,     // a refcount dropped below zero
-  kErrBadBlock = 4,         // a table entry outside [0, num_blocks)
+  kErrBadBlock = 4,         // a table entry outside [0, num_blocks), or not the block the plan saw
 };
 
 constexpr int kMaxArgBlocks = 256;  // new blocks one decode step can hand to its launch

@@ -13,7 +13,7 @@ import torch
 from _parity import assert_attn_close, replay
 from oracle.attention import decode_attention
 from oracle.formats import e4m3fn_to_f64
-from paper_2608_08020_amd.gambit import Pool
+from paper_2608_08020_amd.gambit import GambitError, Pool
 from workload import Workload, tiny
 
 pytestmark = pytest.mark.gpu
@@ -116,3 +116,31 @@ def test_merge_of_one_to_many_partials():
         K, V = (torch.cat([a, b[t:t + 1]]).double().numpy() for a, b in ((k, kn), (v, vn)))
         assert_attn_close(out[t], decode_attention(q[t].double().numpy(), K, V, 1 / math.sqrt(128)), f"{len(K)} tokens")
     p.pool_check()
+
+
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("shared", [False, True])  # narrow units, or cooperative items
+@pytest.mark.parametrize("entry", [0, 3])
+@pytest.mark.parametrize("bad", ["outside", "none", "another"])
+def test_a_table_entry_that_is_not_the_plans_is_reported(kv_dtype, shared, entry, bad):
+    """The first blocks of a unit come with the unit; a device table that says
+    otherwise still sets the error word, as it does for every later block."""
+    T, Hq = (12, 16) if shared else (2, 4)
+    p = Pool(num_blocks=64, num_q_heads=Hq, num_kv_heads=1, max_traces=T, max_blocks_per_trace=16, kv_dtype=kv_dtype)
+    for c in (p.k_cache, p.v_cache):
+        c.view(torch.uint8).zero_()
+    p.kv_alloc([0], [112])
+    if shared:
+        p.kv_fork([0] * (T - 1), list(range(1, T)))
+    ids = list(range(T)) if shared else [0]
+    q = torch.zeros((len(ids), Hq, 128), dtype=torch.bfloat16, device="cuda")
+    x = torch.zeros((len(ids), 1, 128), dtype=torch.bfloat16 if kv_dtype == "bf16" else torch.uint8, device="cuda")
+    p.decode_attn(ids, q, x, x)
+    p.pool_check()
+    good = p.block_table[0, entry].clone()
+    p.block_table[0, entry] = {"outside": 64 + 5, "none": -1, "another": int(good) + 9}[bad]
+    p.decode_attn(ids, q, x, x)
+    p.block_table[0, entry] = good
+    with pytest.raises(GambitError) as e:
+        p.pool_check()
+    assert e.value.code == "DEVICE" and "error word" in str(e.value)

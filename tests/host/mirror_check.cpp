@@ -7,7 +7,7 @@
 // host threads) and staging copies into the caller's workspace.
 //
 // Protocol: one operation per input line, one JSON object per output line.
-//   create NB HQ HKV T MAXB SPLITS      a bf16 pool (workspace, tables in host memory)
+//   create NB HQ HKV T MAXB SPLITS FP8  a pool (workspace, tables in host memory)
 //   alloc  t n [t n ...]                gambit_kv_alloc
 //   write  t pos0 n                     gambit_kv_write (dummy K/V pointers)
 //   fork   p c [p c ...]                gambit_kv_fork
@@ -56,6 +56,7 @@ namespace {
 struct Buffers {
   std::vector<uint8_t> kc, vc, ws_raw;
   std::vector<int32_t> table, seq, ref;
+  float scale[2];
 };
 
 void print_ints(std::ostream& o, const int32_t* a, size_t n) {
@@ -90,7 +91,7 @@ void dump_plan(gambit_pool* p, int st) {
     const int32_t* mem = ws_ptr<int32_t>(p, p->L.members);
     const int32_t* nk = ws_ptr<int32_t>(p, p->L.nk);
     const int32_t* list = ws_ptr<int32_t>(p, p->L.list);
-    o << ",\"grid\":" << p->grid << ",\"kmax\":" << p->L.kmax << ",\"xcd_off\":";
+    o << ",\"grid\":" << p->grid << ",\"kmax\":" << p->L.kmax << ",\"delta\":" << p->step.delta << ",\"xcd_off\":";
     print_ints(o, p->xcd_off, 9);
     o << ",\"list\":";
     print_ints(o, list, n);
@@ -102,7 +103,11 @@ void dump_plan(gambit_pool* p, int st) {
     for (int u = 0; u < p->n_units; ++u) {
       const AttnUnit& a = U[u];
       o << (u ? "," : "") << "[" << a.owner << "," << a.jb0 << "," << a.nblk << "," << a.kvh << "," << a.mem_off
-        << "," << a.mem_cnt << "," << a.kidx << "," << a.flags << "]";
+        << "," << a.mem_cnt << "," << a.kidx << "," << a.flags << ",";
+      print_ints(o, a.pos, 4);
+      o << ",";
+      print_ints(o, a.first, 4);
+      o << "]";
     }
     int max_mem = 0;
     for (int u = 0; u < p->n_units; ++u) max_mem = std::max(max_mem, U[u].mem_off + U[u].mem_cnt);
@@ -137,7 +142,8 @@ int main() {
       d.num_q_heads = a[1];
       d.num_kv_heads = a[2];
       d.head_dim = 128;
-      d.kv_dtype = GAMBIT_KV_BF16;
+      d.kv_dtype = a[6] ? GAMBIT_KV_FP8_E4M3 : GAMBIT_KV_BF16;
+      d.kv_scale = a[6] ? B.scale : nullptr;
       d.max_traces = a[3];
       d.max_blocks_per_trace = a[4];
       d.max_splits = a[5];
@@ -170,7 +176,8 @@ int main() {
       }
       st = gambit_kv_alloc(p, (int)ids.size(), ids.data(), nt.data(), nullptr);
     } else if (op == "write") {
-      st = gambit_kv_write(p, a[0], a[1], a[2], dummy.data(), dummy.data(), nullptr, nullptr);
+      st = gambit_kv_write(p, a[0], a[1], a[2], dummy.data(), dummy.data(),
+                           p->d.kv_scale ? reinterpret_cast<const float*>(dummy.data()) : nullptr, nullptr);
     } else if (op == "fork") {
       std::vector<int32_t> par, ch;
       for (size_t i = 0; i + 1 < a.size(); i += 2) {

@@ -11,7 +11,9 @@ lengths, block rows, refcounts and free count bit-exact, the same error
 for a call the model rejects, and nothing changed by a rejected call.
 Every plan a decode step launches must cover each listed trace's context
 exactly once per KV head with the blocks its own row lists, use each of the
-trace's partial slots exactly once, and report the step's statistics.
+trace's partial slots exactly once, carry in each unit the members, block ids
+and length that its wave would otherwise read, and report the step's
+statistics.
 """
 from __future__ import annotations
 
@@ -163,7 +165,7 @@ def _check_plan(plan, m: PoolModel, Hkv, g, where):
             # up to 128 rows; the last item of a wide chunk takes what is
             # left, as little as one member
             assert 0 < slot[0][5] * g <= 128, where
-        for owner, jb0, nblk, kvh, moff, mcnt, kidx, _ in slot:
+        for owner, jb0, nblk, kvh, moff, mcnt, kidx, _, pos4, first in slot:
             if mcnt == 0:
                 continue
             assert 0 <= kvh < Hkv, where
@@ -172,6 +174,16 @@ def _check_plan(plan, m: PoolModel, Hkv, g, where):
             orow = m.table[owner]
             end = len(orow) if nblk < 0 else jb0 + nblk
             assert 0 <= jb0 < end <= len(orow), (where, owner, jb0, nblk)
+            # what a wave takes from the unit instead of memory: its first
+            # members, its first blocks (of an open unit, those there at plan
+            # time), and an open unit's length at plan time
+            k4 = min(mcnt, 4)
+            assert pos4[:k4] == members[:k4], where
+            had = end
+            if nblk < 0:
+                assert pos4[1] + plan["delta"] == m.seq_len[owner] and plan["delta"] >= 1, (where, pos4, plan["delta"])
+                had = -(-pos4[1] // 16)
+            assert first == [orow[j] if j < had else -1 for j in range(jb0, jb0 + 4)], (where, owner, jb0, nblk, first)
             for pos in members:
                 t = ids[pos]
                 assert m.table[t][jb0:end] == orow[jb0:end], (where, "unit reads blocks not in the member's row")
@@ -196,8 +208,8 @@ def _check_plan(plan, m: PoolModel, Hkv, g, where):
     assert plan["stats"] == [total, uniq_tok, len(used), sum(len(m.table[t]) for t in ids)], where
 
 
-def replay_ops(exe, ops, *, nb, Hq, Hkv, T, maxb, splits):
-    lines = [f"create {nb} {Hq} {Hkv} {T} {maxb} {splits}", "state"]
+def replay_ops(exe, ops, *, nb, Hq, Hkv, T, maxb, splits, fp8=False):
+    lines = [f"create {nb} {Hq} {Hkv} {T} {maxb} {splits} {int(fp8)}", "state"]
     for op in ops:
         lines.append(_line(op))
         lines.append("state")
@@ -236,13 +248,15 @@ SHAPES = [(8, 2), (32, 8), (16, 1), (64, 8), (4, 4)]
 
 
 @settings(max_examples=25, deadline=None, suppress_health_check=[HealthCheck.function_scoped_fixture])
-@given(seed=st.integers(0, 2 ** 31 - 1), shape=st.sampled_from(SHAPES), splits=st.sampled_from([0, 4, 64]))
-def test_mirror_and_planner_match_the_pool_model_under_asan_ubsan(harness, seed, shape, splits):
+@given(seed=st.integers(0, 2 ** 31 - 1), shape=st.sampled_from(SHAPES), splits=st.sampled_from([0, 4, 64]),
+       fp8=st.booleans())
+def test_mirror_and_planner_match_the_pool_model_under_asan_ubsan(harness, seed, shape, splits, fp8):
     rng = random.Random(seed)
     Hq, Hkv = shape
     T = rng.choice([6, 12, 40])
     nb = rng.choice([40, 120, 400])
-    replay_ops(harness["asan"], random_ops(rng, T, 60, nb), nb=nb, Hq=Hq, Hkv=Hkv, T=T, maxb=24, splits=splits)
+    replay_ops(harness["asan"], random_ops(rng, T, 60, nb), nb=nb, Hq=Hq, Hkv=Hkv, T=T, maxb=24, splits=splits,
+               fp8=fp8)
 
 
 def test_large_population_under_asan_ubsan(harness):
@@ -270,3 +284,14 @@ def test_planner_threads_under_tsan(harness):
         ops.append(("fork", list(zip(rng.sample(survivors, 40), victims))))
     plans = replay_ops(harness["tsan"], ops, nb=6000, Hq=32, Hkv=8, T=T, maxb=40, splits=0)
     assert plans == 30
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+def test_runs_wider_than_one_item(harness, fp8):
+    """Runs that 45 traces share, cut into items of 8 to 32 members, over
+    steps that open blocks with the plan they began with."""
+    for Hq, Hkv in ((16, 1), (32, 8), (8, 1)):
+        ids = list(range(45))
+        ops = [("alloc", [(0, 100)]), ("fork", [(0, t) for t in ids[1:]])]
+        ops += [("decode", ids)] * 18 + [("free", ids[40:43])] + [("decode", ids[40::-1])] * 3
+        assert replay_ops(harness["asan"], ops, nb=400, Hq=Hq, Hkv=Hkv, T=45, maxb=12, splits=0, fp8=fp8) == 21

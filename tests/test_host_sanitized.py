@@ -293,5 +293,5 @@ def test_runs_wider_than_one_item(harness, fp8):
     for Hq, Hkv in ((16, 1), (32, 8), (8, 1)):
         ids = list(range(45))
         ops = [("alloc", [(0, 100)]), ("fork", [(0, t) for t in ids[1:]])]
-        ops += [("decode", ids)] * 18 + [("free", ids[40:43])] + [("decode", ids[40::-1])] * 3
+        ops += [("decode", ids)] * 18 + [("free", ids[40:43])] + [("decode", ids[39::-1])] * 3
         assert replay_ops(harness["asan"], ops, nb=400, Hq=Hq, Hkv=Hkv, T=45, maxb=12, splits=0, fp8=fp8) == 21

@@ -636,9 +636,17 @@ gambit_status build_plan(gambit_pool* p, int n, const int32_t* ids, hipStream_t 
   // (bf16) of the narrow slots by count, per pass of 16 steps: 256 traces fp8
   // 3716 -> 3597 us, 512 traces 15024 -> 14661 us, 256 private traces 9218 ->
   // 9151 us, six layers of 45 traces 1688 -> 1591 us, 64 traces 1519 ->
-  // 1530 us.  bf16 weighs cooperative items 1.25 times their time (HBM-bound
-  // units beside them from early on): 1.0 gives 14681 and 9294 us, 1.5 14594
-  // and 9288 us; fp8 (bound by instruction issue) at 1.5: 3880 us.
+  // 1530 us.  bf16 weighs cooperative items 1.25 times their time.  Measured
+  // only, over 37 bf16 and 29 fp8 populations of 8 to 512 traces (private and
+  // branched): cooperative times 0.8, 1.2 and 1.5 times these give passes 0.6,
+  // 0.5, 0.8% (bf16) and 1.8, -0.3, 0.3% (fp8) longer on average, single ones
+  // -5 to +8%.  Other orders on the same populations: by count over the first
+  // 50% or 85%, or by time over 50 to 100% of the narrow slots' time, are a few
+  // percent slower wherever a launch is under ~200 us and -5 to +4% beyond; no
+  // rule on shares or lengths tells those apart.  An item's time goes by its
+  // rows, also that of a wide run's last item with few of them: pricing it as
+  // the others and keeping a run's items next to each other moved one
+  // population by -6%, the others by under 2%.
   std::vector<AttnUnit> units;
   units.reserve(4 * gunits.size() + 8 * gambit::kUnitsPerWG);  // a cooperative item fills a 4-entry slot
   const AttnUnit empty{};

@@ -37,11 +37,6 @@ __device__ inline float wave_max(float v) {
   return v;
 }
 
-__device__ inline float load_elem(const void* p, size_t i, bool bf16) {
-  if (bf16) return __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(p)[i] << 16);
-  return reinterpret_cast<const float*>(p)[i];
-}
-
 __device__ inline float gelu_erf(float x) { return 0.5f * x * (1.f + erff(x * 0.70710678118654752f)); }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));

@@ -752,11 +752,11 @@ __device__ void narrow_unit(const DevPool& P, const AttnLaunch& A, const AttnUni
   }
   f32x4 s0[RB], s1[RB];
   scores(ta, s0, s1);
-  ids.check_first(U);
   if (ntile > 2) {
     if (open) __builtin_amdgcn_s_waitcnt(0);  // the appended token is in the cache before its tile is read
     meta(2, na);
     fetch_k(na, ta);
+    ids.check_first(U);
   }
   // FULL: tiles i + 1 .. i + 3 exist and tile i is whole.  Nothing is
   // conditional then, so the compiler counts the loads in flight and a wait
@@ -804,6 +804,7 @@ __device__ void narrow_unit(const DevPool& P, const AttnLaunch& A, const AttnUni
     step(std::false_type{}, i, ta, ma, na, tb, nb);
     if (i + 1 < ntile) step(std::false_type{}, i + 1, tb, mb, nb, ta, na);
   }
+  if (ntile <= 2) ids.check_first(U);  // no tile waited for the table
 #pragma unroll
   for (int r = 0; r < RB; ++r) write_partial<STREAM>(A, U, qrow[r], g.q, st[r]);
 }
@@ -1022,6 +1023,8 @@ __device__ void coop_unit(const DevPool& P, const AttnLaunch& A, const AttnUnit&
   if (ntile > 1) move(1, U.first[2], nblk > 3 ? U.first[3] : U.first[2]);
   fetch_ids(0);
   if (nblk > 64) fetch_ids(1);
+  int entry = 0;  // the table's first entries, compared at the end with the ids that the unit carries
+  if (t < min(nblk, 4)) entry = brow[t];
 #pragma unroll
   for (int r = 0; r < RB; ++r) {
     qrow[r] = query_row(A, U, P.Hq, row0 + 16 * r, R, g.lr);
@@ -1031,10 +1034,6 @@ __device__ void coop_unit(const DevPool& P, const AttnLaunch& A, const AttnUnit&
   __builtin_amdgcn_s_waitcnt(0x0F70);  // all of them are in
   barrier_no_fence();
   for (int i = 2; i < ahead && i < ntile; ++i) issue(i);
-  if (t < min(nblk, 4)) {  // the table's first entries are the ids that the unit carries
-    const int want = t == 0 ? U.first[0] : t == 1 ? U.first[1] : t == 2 ? U.first[2] : U.first[3];
-    if (idw[t] != want) atomicOr(P.err, kErrBadBlock);
-  }
   f32x4 s0[RB], s1[RB];
   if (active) qk(lds, s0, s1);
   // Iteration i issues the scores of tile i + 1 before the softmax and P.V
@@ -1060,6 +1059,10 @@ __device__ void coop_unit(const DevPool& P, const AttnLaunch& A, const AttnUnit&
   if (active) {
 #pragma unroll
     for (int r = 0; r < RB; ++r) write_partial<STREAM>(A, U, qrow[r], g.q, st[r]);
+  }
+  if (t < min(nblk, 4)) {
+    const int want = t == 0 ? U.first[0] : t == 1 ? U.first[1] : t == 2 ? U.first[2] : U.first[3];
+    if (entry != want) atomicOr(P.err, kErrBadBlock);
   }
 }
 

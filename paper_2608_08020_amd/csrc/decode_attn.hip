@@ -1133,15 +1133,19 @@ __global__ __launch_bounds__(kThreads, 2) void attn_units_kernel(DevPool P, Attn
 // Log-sum-exp merge of a row's partials.  One wave per (list position,
 // query head): lane k < nk reads partial k's (max, sum) and the wave reduces
 // the maximum and the weighted sum, while the partials themselves are already
-// on their way: half-wave h reads partials 2 j + h whole (16 bytes a lane), up
-// to kMergeDepth of them per half requested before the first is used (an odd
-// count's last partial by both halves, added by one).  Each half adds its
+// on their way: half-wave h reads partials 2 j + h whole (16 bytes a lane),
+// all of a pass requested before the first is used.  Each half adds its
 // partials in order; the two halves' sums are added last.  Bound by latency at
 // small populations (a row's partials are 2-10 KB) and by HBM at large ones
-// (0.1 GB at 512 traces).  Loads past nk are left out by the wave: clamped to
-// the last partial instead, a row of one partial read it 16 times (512 traces
-// of one partial 11.4 -> 7.6 us; two to six of them, 256 private traces, 8.8 ->
-// 6.8 us; 512 branched traces 18.3 -> 16.0 us).
+// (0.1 GB at 512 traces).  The loads a pass asks for (per half 1, 2, 4 or
+// kMergeDepth) go by the row's count, so that at most half of them fall past
+// nk, where they are clamped to the last partial and left out of the sums;
+// within a pass nothing is conditional.  Per merge, kMergeDepth loads for every
+// row / only a row's own, each under its own condition / these passes: 512
+// traces of one partial 11.4 / 8.0 / 8.1 us, 256 private traces 8.7 / 6.4 /
+// 6.0, 512 branched traces 17.8 / 15.5 / 15.5, 64 traces 6.4 / 6.1 / 5.7, 20
+// branched traces 5.5 / 5.7 / 5.2 (conditions made each addition
+// wait for its own weight and load).
 constexpr int kMergeDepth = 8;
 
 // The merge's part of a launch.  The attention launch's own arguments, with
@@ -1177,33 +1181,43 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeLaunch A) {
   const float2* ml = A.part_ml + (size_t)row * A.kmax;
   const float* pa = A.part_acc + (size_t)row * A.kmax * kHeadDim + 4 * (lane & 31);
   const float2 mine = lane < nk ? ml[lane] : float2{-INFINITY, 0.f};
-  f32x4 a[kMergeDepth];
-  auto load = [&](int k0) {
+  float L;
+  f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto gather = [&](auto depth) {
+    constexpr int D = decltype(depth)::value;
+    f32x4 a[D];
+    auto load = [&](int k0) {
 #pragma unroll
-    for (int j = 0; j < kMergeDepth; ++j)
-      if (k0 + 2 * j < nk)
+      for (int j = 0; j < D; ++j)
         a[j] = __builtin_nontemporal_load(
             reinterpret_cast<const f32x4*>(pa + (size_t)min(k0 + 2 * j + half, nk - 1) * kHeadDim));
-  };
-  load(0);
-  float M = mine.x;
+    };
+    load(0);
+    float M = mine.x;
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-  const float w = lane < nk ? exp2f(mine.x - M) : 0.f;
-  float L = w * mine.y;
+    for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
+    const float w = lane < nk ? exp2f(mine.x - M) : 0.f;
+    L = w * mine.y;
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) L += __shfl_xor(L, off);
-  f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < nk; k0 += 2 * kMergeDepth) {
-    if (k0) load(k0);
+    for (int off = 32; off > 0; off >>= 1) L += __shfl_xor(L, off);
+    for (int k0 = 0; k0 < nk; k0 += 2 * D) {
+      if (k0) load(k0);
 #pragma unroll
-    for (int j = 0; j < kMergeDepth; ++j) {
-      if (k0 + 2 * j >= nk) break;
-      const int k = k0 + 2 * j + half;  // <= 63
-      const float wk = __shfl(w, k);
-      if (k < nk) o += wk * a[j];
+      for (int j = 0; j < D; ++j) {
+        const int k = k0 + 2 * j + half;  // <= 63
+        const float wk = __shfl(w, k);
+        if (k < nk) o += wk * a[j];
+      }
     }
-  }
+  };
+  if (nk <= 2)
+    gather(std::integral_constant<int, 1>{});
+  else if (nk <= 4)
+    gather(std::integral_constant<int, 2>{});
+  else if (nk <= 8)
+    gather(std::integral_constant<int, 4>{});
+  else
+    gather(std::integral_constant<int, kMergeDepth>{});
   const float inv = 1.f / L;
 #pragma unroll
   for (int e = 0; e < 4; ++e) o[e] = (o[e] + __shfl_xor(o[e], 32)) * inv;
